@@ -368,11 +368,7 @@ pir_status pir_db_load_ntt(pir_db *db, const uint32_t *src, uint32_t row0, uint3
         for (uint32_t r = 0; r < nrows; r += rows_tmp) {
             const uint32_t nr = std::min(rows_tmp, nrows - r);
             const uint32_t *s = src + (uint64_t)r * row_words;
-            for (uint32_t l = 0; l < p.nprimes; ++l) {
-                const NttTables &t = ntt_tables(p.q[l], p.n);
-                launch_ntt(s + (uint64_t)l * p.n, tmp + (uint64_t)l * p.n, (uint64_t)nr * p.d1, poly, poly,
-                           t, false, st);
-            }
+            launch_ntt(s, tmp, (uint64_t)nr * p.d1, p.n, p.nprimes, p.q, false, st);
             if (db->layouts & PIR_LAYOUT_VALU) launch_db_layout_valu(*db, tmp, row0 + r, nr, st);
             if (db->layouts & PIR_LAYOUT_MFMA) launch_db_layout_mfma(*db, tmp, row0 + r, nr, st);
         }
@@ -482,8 +478,7 @@ static pir_status ntt_entry(const uint32_t *in, uint32_t *out, uint32_t count, u
         PIR_REQUIRE(q % (2 * n) == 1 && is_prime_u32(q), "q must be a prime with q = 1 mod 2n");
         if (count == 0) return;
         PIR_REQUIRE(in && out, "NULL pointer");
-        const NttTables &t = ntt_tables(q, n);
-        launch_ntt(in, out, count, n, n, t, inverse, as_stream(stream));
+        launch_ntt(in, out, count, n, 1, &q, inverse, as_stream(stream));
     });
 }
 

@@ -212,8 +212,10 @@ bool env_flag(const char *name);
 
 // ---------------------------------------------------------------- launchers
 // Defined in the kernel translation units; all enqueue on `st`.
-void launch_ntt(const uint32_t *in, uint32_t *out, uint64_t count, uint64_t in_stride,
-                uint64_t out_stride, const NttTables &t, bool inverse, hipStream_t st);
+// NTT of `records` records of L polynomials of n words (limb l mod q[l]); in
+// may equal out.
+void launch_ntt(const uint32_t *in, uint32_t *out, uint64_t records, uint32_t n, uint32_t L, const uint32_t *q,
+                bool inverse, hipStream_t st);
 void launch_db_layout_valu(const pir_db &db, const uint32_t *ntt_src, uint32_t row0,
                            uint32_t nrows, hipStream_t st);
 void launch_db_layout_mfma(const pir_db &db, const uint32_t *ntt_src, uint32_t row0,
@@ -231,7 +233,10 @@ void launch_rowsel_mfma(const pir_db &db, const uint32_t *q, uint32_t B, uint32_
                         hipStream_t st, bool q_coeff = false);
 // Query front end: coefficient-domain query -> NTT-domain query, both in the
 // boundary layout [B][2][D0][L][N].
-void launch_query_ntt(const pir_db &db, const uint32_t *q_coeff, uint32_t B, uint32_t *q_ntt, hipStream_t st);
+inline void launch_query_ntt(const pir_db &db, const uint32_t *q_coeff, uint32_t B, uint32_t *q_ntt,
+                             hipStream_t st) {
+    launch_ntt(q_coeff, q_ntt, 2ull * B * db.p.d0, db.p.n, db.p.nprimes, db.p.q, false, st);
+}
 
 // First ColTor stage (coltor.hip).
 void coltor_check_gadget(const pir_params &ring, uint32_t log2z, uint32_t ell);
