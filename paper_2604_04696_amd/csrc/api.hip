@@ -20,14 +20,14 @@ void set_error(const std::string &msg) { g_last_error = msg; }
 void clear_error() { g_last_error.clear(); }
 
 // ------------------------------------------------------------------ memory
-static void trim_scratch_pool();
+static void trim_scratch();
 
 void *dev_alloc(size_t bytes) {
     void *p = nullptr;
     hipError_t e = hipMalloc(&p, bytes ? bytes : 1);
-    if (e != hipSuccess) {   // once more without the scratch pool's free blocks
+    if (e != hipSuccess) {   // once more without the kept scratch blocks
         (void)hipGetLastError();
-        trim_scratch_pool();
+        trim_scratch();
         e = hipMalloc(&p, bytes ? bytes : 1);
     }
     if (e != hipSuccess) {
@@ -44,78 +44,144 @@ void dev_free(void *p) {
 DevBuf::DevBuf(size_t n) : ptr(dev_alloc(n)), bytes(n) {}
 DevBuf::~DevBuf() { dev_free(ptr); }
 
-// Scratch comes from a memory pool of the library's own, one per device.  The
-// device's default pool gives every free block back at each synchronization,
-// so a program that waits for its results paid for mapping the scratch again
-// on the next call: with coefficient-domain selectors of 32 clients and a
-// first ColTor stage (8 GiB DB) a new caller's first pass took 50 ms where a
-// repeated one takes 8, and a waited-for pass with 64 clients up to 113 ms
-// against 5.6.
-// This pool keeps at most SCRATCH_KEEP bytes of free blocks across
-// synchronizations (enough for the scratch of 64 clients on an 8 GiB DB, query
-// transform included).  It gives them back when a DB is freed and when an
-// allocation of the library fails.  The runtime orders the reuse of a block
-// between streams and threads.
+// Scratch blocks are kept by the library when a call is done with them, and the
+// next call on the same stream takes them up again.  Both of the runtime's
+// pools cost more than the work they served: the default one gives every free
+// block back at each synchronization (a waited-for call with 64 clients took up
+// to 113 ms against 5.6), and a pool that keeps its blocks made every
+// allocation wait until the stream had drained, so no call was ever queued
+// behind another (nine chained ColTor stages of one client: 1.5 ms, and up to
+// 6.6 ms, for 0.65 ms of kernels).
+//
+// A block goes back with an event recorded behind its last use, and whoever
+// takes it up waits for that event on its own stream (no wait at all where the
+// two are the same stream): a recycled stream handle or the per-thread default
+// stream, one handle for many streams, is ordered like any other.  Blocks are
+// not moved between stream handles: two streams never wait for each other's
+// scratch.  At most SCRATCH_KEEP bytes per device wait for a user (enough for
+// 64 clients on an 8 GiB DB, query transform included); the longest unused
+// ones go first, and all of them when a DB is freed or an allocation of the
+// library fails.  The memory itself comes from hipMallocAsync, as in captured
+// calls, whose allocations become nodes of the graph.
 constexpr uint64_t SCRATCH_KEEP = 8ull << 30;
-constexpr int MAX_POOLS = 64;
 
-// The current device's pool; nullptr where none can be made (the default pool
-// serves then).
-static std::mutex g_pools_mu;
-static hipMemPool_t g_pools[MAX_POOLS];
+struct ScratchBlock {
+    void *ptr;
+    size_t bytes;
+    hipStream_t st;     // the stream that used it last
+    hipEvent_t done;    // behind that use
+    int device;
+};
 
-static hipMemPool_t scratch_pool(bool make) {
+static std::mutex g_scratch_mu;
+static std::vector<ScratchBlock> g_scratch;   // free blocks, the longest unused first
+
+// Gives a free block's memory back, in order on st (any stream of its device).
+static void release_block(const ScratchBlock &b, hipStream_t st) {
+    if (hipStreamWaitEvent(st, b.done, 0) == hipSuccess) {
+        (void)hipFreeAsync(b.ptr, st);
+    } else {
+        (void)hipGetLastError();
+        (void)hipFree(b.ptr);   // waits for the device
+    }
+    (void)hipEventDestroy(b.done);
+}
+
+// Gives back the current device's free blocks.
+static void trim_scratch() {
     int dev = 0;
-    PIR_HIP(hipGetDevice(&dev));
-    if (dev < 0 || dev >= MAX_POOLS) return nullptr;
-    std::lock_guard<std::mutex> lk(g_pools_mu);
-    if (!g_pools[dev] && make) {
-        hipMemPoolProps props{};
-        props.allocType = hipMemAllocationTypePinned;
-        props.location.type = hipMemLocationTypeDevice;
-        props.location.id = dev;
-        hipMemPool_t pool = nullptr;
-        uint64_t keep = SCRATCH_KEEP;
-        if (hipMemPoolCreate(&pool, &props) != hipSuccess ||
-            hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep) != hipSuccess) {
-            (void)hipGetLastError();
-            if (pool) (void)hipMemPoolDestroy(pool);
-            return nullptr;
+    if (hipGetDevice(&dev) != hipSuccess) return;
+    std::lock_guard<std::mutex> lk(g_scratch_mu);
+    std::vector<ScratchBlock> kept;
+    for (const ScratchBlock &b : g_scratch) {
+        if (b.device != dev) {
+            kept.push_back(b);
+            continue;
         }
-        g_pools[dev] = pool;
+        (void)hipEventSynchronize(b.done);
+        (void)hipFree(b.ptr);
+        (void)hipEventDestroy(b.done);
     }
-    return g_pools[dev];
+    g_scratch.swap(kept);
 }
 
-static void trim_scratch_pool() {
-    if (hipMemPool_t pool = scratch_pool(false)) (void)hipMemPoolTrimTo(pool, 0);
-}
-
-StreamScratch::StreamScratch(size_t bytes, hipStream_t s) : st(s) {
-    if (bytes == 0) return;
-    // (under stream capture the allocation becomes a node of the graph, as
-    // from the default pool)
+// Whether st is being captured (or cannot say).
+static bool capturing(hipStream_t st) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+    if (hipStreamIsCapturing(st, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
+StreamScratch::StreamScratch(size_t need, hipStream_t s) : st(s) {
+    if (need == 0) return;
+    bytes = need;
+    PIR_HIP(hipGetDevice(&device));
+    keep = !capturing(st);
+    if (keep) {
+        // the smallest block that fits, unless it is far larger than asked for
+        std::lock_guard<std::mutex> lk(g_scratch_mu);
+        size_t best = g_scratch.size();
+        for (size_t i = 0; i < g_scratch.size(); ++i) {
+            const ScratchBlock &b = g_scratch[i];
+            if (b.device == device && b.st == st && b.bytes >= need && b.bytes / 4 <= need + (1u << 20) &&
+                (best == g_scratch.size() || b.bytes < g_scratch[best].bytes))
+                best = i;
+        }
+        if (best < g_scratch.size() && hipStreamWaitEvent(st, g_scratch[best].done, 0) == hipSuccess) {
+            ptr = g_scratch[best].ptr;
+            bytes = g_scratch[best].bytes;
+            done = g_scratch[best].done;
+            g_scratch.erase(g_scratch.begin() + best);
+            return;
+        }
         (void)hipGetLastError();
-        cap = hipStreamCaptureStatusActive;
+        if (hipEventCreateWithFlags(&done, hipEventDisableTiming) != hipSuccess) {
+            (void)hipGetLastError();
+            done = nullptr;
+            keep = false;
+        }
     }
-    hipMemPool_t pool = cap == hipStreamCaptureStatusNone ? scratch_pool(true) : nullptr;
-    hipError_t e = pool ? hipMallocFromPoolAsync(&ptr, bytes, pool, st) : hipMallocAsync(&ptr, bytes, st);
-    if (e != hipSuccess && pool) {   // free blocks of other sizes may hold the memory
+    hipError_t e = hipMallocAsync(&ptr, bytes, st);
+    if (e != hipSuccess && keep) {   // once more without the kept blocks
         (void)hipGetLastError();
-        (void)hipMemPoolTrimTo(pool, 0);
-        e = hipMallocFromPoolAsync(&ptr, bytes, pool, st);
+        trim_scratch();
+        e = hipMallocAsync(&ptr, bytes, st);
     }
     if (e != hipSuccess) {
         ptr = nullptr;
+        if (done) (void)hipEventDestroy(done);
         (void)hipGetLastError();
         PIR_FAIL(e == hipErrorOutOfMemory ? PIR_ENOMEM : PIR_EDEVICE, "hipMallocAsync(%zu bytes) failed: %s",
                  bytes, hipGetErrorString(e));
     }
 }
+
 StreamScratch::~StreamScratch() {
-    if (ptr) (void)hipFreeAsync(ptr, st);
+    if (!ptr) return;
+    if (!keep || bytes > SCRATCH_KEEP || hipEventRecord(done, st) != hipSuccess) {
+        if (done) (void)hipEventDestroy(done);
+        (void)hipFreeAsync(ptr, st);
+        return;
+    }
+    try {
+        std::lock_guard<std::mutex> lk(g_scratch_mu);
+        uint64_t total = bytes;
+        for (const ScratchBlock &b : g_scratch) total += b.device == device ? b.bytes : 0;
+        for (size_t i = 0; total > SCRATCH_KEEP && i < g_scratch.size();) {
+            if (g_scratch[i].device != device) {
+                ++i;
+                continue;
+            }
+            total -= g_scratch[i].bytes;
+            release_block(g_scratch[i], st);
+            g_scratch.erase(g_scratch.begin() + i);
+        }
+        g_scratch.push_back({ptr, bytes, st, done, device});
+    } catch (...) {
+        (void)hipFreeAsync(ptr, st);
+        (void)hipEventDestroy(done);
+    }
 }
 
 // ------------------------------------------------------------- kernel timer
@@ -397,7 +463,7 @@ void pir_db_free(pir_db *db) {
         DeviceGuard dg(db->device);
         (void)hipDeviceSynchronize();
         release_group_plans(db);
-        trim_scratch_pool();
+        trim_scratch();
     } catch (...) {
     }
     dev_free(db->valu.data);

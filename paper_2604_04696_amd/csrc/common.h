@@ -181,13 +181,18 @@ struct DeviceGuard {
 void *dev_alloc(size_t bytes);   // throws PIR_ENOMEM
 void dev_free(void *p);
 
-// Stream-ordered temporary: hipMallocAsync on `st` at construction,
-// hipFreeAsync on the same stream when the scope ends (also when a later
-// step of the call throws).  Allocation failure throws PIR_ENOMEM.
+// Stream-ordered temporary: a block that an earlier call on `st` left behind, or
+// a new one, at construction; handed back in stream order when the scope ends
+// (also when a later step of the call throws).  Allocation failure throws
+// PIR_ENOMEM.
 struct StreamScratch {
     void *ptr = nullptr;
     hipStream_t st = nullptr;
-    StreamScratch(size_t bytes, hipStream_t s);
+    size_t bytes = 0;             // of the block (at least what was asked for)
+    hipEvent_t done = nullptr;    // recorded when it is handed back
+    int device = 0;
+    bool keep = false;            // handed back to the library, not to the runtime
+    StreamScratch(size_t need, hipStream_t s);
     ~StreamScratch();
     StreamScratch(const StreamScratch &) = delete;
     StreamScratch &operator=(const StreamScratch &) = delete;
