@@ -51,6 +51,8 @@ void launch_mfma_grouped(const MfmaJob &one, const MfmaJob *jobs_dev, uint32_t n
 // Tile shape for one job of mp rows and d1 columns (serving steps); deep: run
 // it through launch_mfma_grouped's fixed-shape kernel.
 void pick_shape(uint32_t mp, uint32_t d1, uint32_t *pts, uint32_t *wm, bool *deep);
+// whether PIR_GROUPED_SHAPE or PIR_GROUPED_RING names a tile shape or a kernel
+bool shape_forced();
 // A job for that kernel in tile shape pts x 32wm x 32wn (pts * wm * wn = 8).
 MfmaJob make_shaped_job(const pir_db &db, const int8_t *qd, uint32_t *out, uint32_t B, uint32_t pts, uint32_t wm);
 // The query-resident kernel (rowsel_mfma_qres.hip) for mp <= 128 rows
@@ -68,6 +70,11 @@ uint32_t qres_min_chunks(uint32_t shape);   // 64-row chunks of k the kernel nee
 MfmaJob make_qres_job(const pir_db &db, const int8_t *qd, uint32_t mstride, uint32_t *stage, uint32_t B,
                       uint32_t shape);
 void launch_mfma_qres(const MfmaJob &job, hipStream_t st);
+// The small-batch kernel (rowsel_mfma_direct.hip): the rows its query planes
+// need for a job of `rows` query rows, 0 where another kernel takes the job.
+// The job's mp is the row stride of its staging (rows past it are dropped).
+uint32_t direct_rows(uint32_t rows);
+void launch_mfma_direct(const MfmaJob &job, hipStream_t st);
 // Staging row stride of a DB with d1 columns (16-byte aligned rows).
 inline uint32_t staging_stride(uint32_t d1) { return (d1 + 3) / 4 * 4; }
 

@@ -1086,13 +1086,15 @@ void launch_query_digits_rows(const pir_db &db, const uint32_t *q, uint32_t rows
 void launch_rowsel_mfma(const pir_db &db, const uint32_t *q, uint32_t B, uint32_t *out,
                         hipStream_t st, bool q_coeff) {
     // scratch: query digit planes [P][4][Kp/64][Mp][64], then the output
-    // staging [P][Mp][sstride]
+    // staging [P][rows][sstride]
     const uint32_t mp = (2 * B + 31) / 32 * 32;
-    const bool qres = qres_preferred(mp, db.mfma.kp / 64);
+    const uint32_t drows = direct_rows(2 * B);
+    const bool qres = !drows && qres_preferred(mp, db.mfma.kp / 64);
     const uint32_t shape = qres_shape_for(mp), bm = qres_rows(shape);
-    const uint32_t mstride = qres ? (mp + bm - 1) / bm * bm : mp;
+    const uint32_t mstride = drows ? drows : qres ? (mp + bm - 1) / bm * bm : mp;
+    const uint32_t srows = drows ? 2 * B : mp;
     const size_t qbytes = ((size_t)db.slots() * 4 * mstride * db.mfma.kp + 255) / 256 * 256;
-    const size_t sbytes = (size_t)db.slots() * mp * staging_stride(db.p.d1) * 4;
+    const size_t sbytes = (size_t)db.slots() * srows * staging_stride(db.p.d1) * 4;
     StreamScratch buf(qbytes + sbytes, st);
     int8_t *scratch = buf.as<int8_t>();
     uint32_t *stage = reinterpret_cast<uint32_t *>(scratch + qbytes);
@@ -1105,7 +1107,13 @@ void launch_rowsel_mfma(const pir_db &db, const uint32_t *q, uint32_t B, uint32_
     } else {
         launch_query_digits_rows(db, q, 2 * B, scratch, mstride, 0, st);
     }
-    if (qres) {
+    if (drows) {
+        MfmaJob job = make_mfma_job(db, scratch, stage, B, 0, 2);
+        job.mp = srows;
+        job.mstride = mstride;
+        KernelTimer::Scope timed(st);
+        launch_mfma_direct(job, st);
+    } else if (qres) {
         const MfmaJob job = make_qres_job(db, scratch, mstride, stage, B, shape);
         KernelTimer::Scope timed(st);
         launch_mfma_qres(job, st);
@@ -1114,7 +1122,7 @@ void launch_rowsel_mfma(const pir_db &db, const uint32_t *q, uint32_t B, uint32_
         KernelTimer::Scope timed(st);
         launch_mfma_jobs(job, nullptr, 1, job.tiles, st);
     }
-    launch_out_transpose(stage, out, 2 * B, mp, db.p.d1, (uint32_t)db.slots(), st);
+    launch_out_transpose(stage, out, 2 * B, srows, db.p.d1, (uint32_t)db.slots(), st);
 }
 
 // ------------------------------------------------------------- grouped
@@ -1277,6 +1285,8 @@ void pick_shape(uint32_t mp, uint32_t d1, uint32_t *pts, uint32_t *wm, bool *dee
     *wm = G_SHAPES[best].wm;
     *deep = G_SHAPES[best].deep_ok() && forced_ring() != 2;
 }
+
+bool shape_forced() { return forced_shape() || forced_ring(); }
 
 // A job of a grouped plan in tile shape `s`.
 static MfmaJob grouped_job(const pir_db &db, const int8_t *qd, uint32_t *stage, uint32_t B, const GShape &s) {

@@ -227,7 +227,16 @@ struct pir_server {
         // (or the query-resident kernel when the rows fill its units)
         const uint32_t mp = (rows + 31) / 32 * 32;
         MfmaJob job;
-        if (qres_preferred(mp, db->mfma.kp / 64)) {
+        // (or, up to 16 clients, the small-batch kernel)
+        if (direct_rows(rows) && !shape_forced()) {
+            job = make_mfma_job(*db, qd, stage, hi + 1, 0, 2);
+            job.mp = rows;
+            job.mstride = mstride;
+            job.g_begin = g_begin;
+            job.groups = ng;
+            KernelTimer::Scope timed(st);
+            launch_mfma_direct(job, st);
+        } else if (qres_preferred(mp, db->mfma.kp / 64)) {
             job = make_qres_job(*db, qd, mstride, stage, hi + 1, qres_shape_for(mp));
             job.g_begin = g_begin;
             job.groups = ng;
