@@ -236,6 +236,8 @@ size_t stream_staging_bytes(const pir_db &db, uint32_t B);
 // q_coeff: the query is in the coefficient domain (transformed first)
 void launch_rowsel_mfma(const pir_db &db, const uint32_t *q, uint32_t B, uint32_t *out,
                         hipStream_t st, bool q_coeff = false);
+// The same from the VALU layout (rowsel_mfma_valu.hip).
+void launch_rowsel_mfma_valu(const pir_db &db, const uint32_t *q, uint32_t B, uint32_t *out, hipStream_t st);
 // Query front end: coefficient-domain query -> NTT-domain query, both in the
 // boundary layout [B][2][D0][L][N].
 inline void launch_query_ntt(const pir_db &db, const uint32_t *q_coeff, uint32_t B, uint32_t *q_ntt,

@@ -164,34 +164,18 @@ __host__ __device__ inline bool combine_direct_ok(uint32_t q) {
 // Balanced signed base-2^8 digits: x = sum_i d_i 2^(8i), d_i in [-128, 127],
 // for -2155905152 <= x <= 2139062143 (-0x80808080 .. 0x7F7F7F7F, the whole
 // reach of four such digits).  Returned packed as four int8 in one 32-bit
-// word, digit i in byte i.  The top digit of 0 <= x < 2^30 stays in [0, 64].
-__device__ __forceinline__ uint32_t split_digits(uint32_t x) {
-    uint32_t packed = 0;
-    int32_t v = (int32_t)x;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        int32_t d = ((v + 128) & 255) - 128;
-        packed |= ((uint32_t)(uint8_t)(int8_t)d) << (8 * i);
-        v = (v - d) >> 8;
-    }
-    return packed;
-}
+// word, digit i in byte i: byte i of x + 0x80808080 is d_i + 128 (the carries
+// between bytes are the balanced recursion's), and the exclusive or takes the
+// 128 off again.  Only x + 0x80808080 in [0, 2^32) matters, so x may be given
+// mod 2^32.  The top digit of 0 <= x < 2^30 stays in [0, 64].
+__device__ __forceinline__ uint32_t split_digits(uint32_t x) { return (x + 0x80808080u) ^ 0x80808080u; }
 
 // The digits of a residue r of any prime q < 2^32.  The reach of four digits
 // holds 2^32 - 1 consecutive integers, so every residue class has a
 // representative in it: x = r for r <= 0x7F7F7F7F, x = r - q above, which is
-// at least 0x7F7F7F80 - q >= -2155905151.  That x may lie below -2^31, so the
-// split runs on 64-bit values.
+// at least 0x7F7F7F80 - q >= -2155905151.
 __device__ __forceinline__ uint32_t split_digits_window(uint32_t r, uint32_t q) {
-    int64_t v = r > 0x7F7F7F7Fu ? (int64_t)r - (int64_t)q : (int64_t)r;
-    uint32_t packed = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int64_t d = ((v + 128) & 255) - 128;
-        packed |= ((uint32_t)(uint8_t)(int8_t)d) << (8 * i);
-        v = (v - d) >> 8;
-    }
-    return packed;
+    return split_digits(r > 0x7F7F7F7Fu ? r - q : r);
 }
 
 // Maps blockIdx.x so that runs of consecutive logical block indices execute

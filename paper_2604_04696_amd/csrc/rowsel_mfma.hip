@@ -1079,8 +1079,8 @@ void launch_query_digits_rows(const pir_db &db, const uint32_t *q, uint32_t rows
                               uint32_t mstride, uint32_t row0, hipStream_t st) {
     const auto &p = db.p;
     const uint32_t P = p.n * p.nprimes;
-    launch_digit_planes(db, q, (uint64_t)p.d0 * P, P, qd, rows, rows, P, db.mfma.kp, 0, p.d0, p.d0, st, mstride,
-                        row0);
+    launch_digit_planes(db, q, (uint64_t)p.d0 * P, P, qd, rows, rows, P, (p.d0 + 63) / 64 * 64, 0, p.d0, p.d0, st,
+                        mstride, row0);
 }
 
 void launch_rowsel_mfma(const pir_db &db, const uint32_t *q, uint32_t B, uint32_t *out,
