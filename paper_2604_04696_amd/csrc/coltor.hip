@@ -29,6 +29,12 @@
 //                      limb's twiddles are staged in LDS, and the next digit
 //                      polynomial is loaded during the current transform);
 //                      then ct0 is added and both output polynomials stored.
+//                      Bound by VALU issue: 8192 nodes at N = 4096, four
+//                      27-bit limbs, ell = 5 take 2.05 ms for 8.1e9
+//                      butterflies, over 80% of the issue slots.  Butterflies
+//                      of six instructions, each twiddle read and waited for
+//                      at its use, four barriers a transform that also waited
+//                      for the loads in flight: 2.42-2.59 ms.
 // The butterfly and sum forms are chosen per launch from the primes: wide
 // (64-bit intermediates) for any prime of 2^30 or more, lazy below, and
 // unreduced forward butterflies when (1 + 2 logN) q < 2^32; the small-ring
@@ -47,9 +53,10 @@ typedef __int128 i128;
 constexpr int CT_THREADS = 512;
 
 struct ColtorPrimes {
-    const uint32_t *fwd[PIR_MAX_PRIMES];   // forward twiddles [n] + Shoup companions [n]
+    const uint32_t *fwd[PIR_MAX_PRIMES];   // forward twiddles [n] + Shoup companions [n] + Montgomery forms [n] + LDS order (NttTables)
     const uint32_t *inv[PIR_MAX_PRIMES];   // inverse twiddles [n] + companions [n]
-    uint32_t q[PIR_MAX_PRIMES];
+    uint32_t q[PIR_MAX_PRIMES], qn[PIR_MAX_PRIMES];        // the primes and -q^-1 mod 2^32
+    uint32_t r1[PIR_MAX_PRIMES];                           // floor(2^32 / q)
     uint32_t ninv[PIR_MAX_PRIMES], ninv_s[PIR_MAX_PRIMES];
     uint32_t crt_c[PIR_MAX_PRIMES], crt_cs[PIR_MAX_PRIMES];   // (Q/q_l)^-1 mod q_l and its companion
     uint32_t crt_cn[PIR_MAX_PRIMES], crt_cns[PIR_MAX_PRIMES]; // the same times N^-1 (folds the INTT scale)
@@ -325,14 +332,14 @@ coltor_mac_kernel(const uint32_t *__restrict__ ct, const uint32_t *__restrict__ 
 }
 
 // ------------------------------- kernel 2, register-blocked (N >= 256)
-// The RGSW rows are first permuted so that word 16t + r of a row holds point
-// bitrev(16t + r) (rgsw_permute_kernel): after the register-blocked forward
-// transform thread t holds exactly those points of a digit polynomial in
-// registers 0..15, so each multiply reads 64 contiguous bytes per thread and
-// no digit polynomial goes back through LDS to natural order.  Products are
-// summed lazily in 64 bits (at most 16 below 2^60 each for q < 2^30;
-// wrap-counting sums for wider primes) and reduced once; the two results
-// then take one LDS exchange each to natural order, where ct0 is added.
+// The RGSW rows are first permuted (rgsw_permute_kernel): after the register-
+// blocked forward transform thread t holds point bitrev(16t + r) of a digit
+// polynomial in register r, so word 4 (g N/16 + t) + k of a permuted row is
+// point bitrev(16t + 4g + k): each multiply reads four coalesced 16-byte
+// vectors per thread and no digit polynomial goes back through LDS to natural
+// order.  Products are summed lazily in 64 bits (at most 16 below 2^60 each
+// for q < 2^30; wrap-counting sums for wider primes) and reduced once; the two
+// results then take one LDS exchange each to natural order, where ct0 is added.
 // One block per row of n words: the row goes to LDS with coalesced loads
 // (padded one word per 64, so that the bit-reversed reads of a wave fall on
 // distinct banks two lanes at a time) and leaves with coalesced stores.  (The
@@ -344,9 +351,10 @@ rgsw_permute_kernel(const uint32_t *__restrict__ in, uint32_t *__restrict__ out,
     const uint64_t base = (uint64_t)blockIdx.x * n;
     for (uint32_t i = threadIdx.x; i < n; i += 256) s[i + (i >> 6)] = in[base + i];
     __syncthreads();
-    for (uint32_t j = threadIdx.x; j < n; j += 256) {
-        const uint32_t k = __brev(j) >> (32 - logn);
-        out[base + j] = s[k + (k >> 6)];
+    const uint32_t T = n / QR;
+    for (uint32_t e = threadIdx.x; e < n; e += 256) {
+        const uint32_t j = e / 4 % T * QR + e / (4 * T) * 4 + e % 4, k = __brev(j) >> (32 - logn);
+        out[base + e] = s[k + (k >> 6)];
     }
 }
 
@@ -357,17 +365,17 @@ coltor_mac_reg_kernel(const uint32_t *__restrict__ ct, const uint32_t *__restric
                       uint32_t nout, uint32_t L, uint32_t ell, ColtorPrimes pr) {
     constexpr uint32_t n = 1u << LOGN, T = n / QR;
     // up to N = 4096 the twiddles are staged in LDS: kept in registers across
-    // the 2 ell transforms they took ~90 VGPRs (236 in all, two waves per
-    // SIMD, 61% of the VALU issue slots used)
-    constexpr bool TW_LDS = LOGN <= 12;
-    extern __shared__ uint32_t s[];                  // n + n/16 words, then (TW_LDS) n twiddle pairs
+    // the 2 ell transforms they took ~90 VGPRs
+    constexpr bool TW_LDS = LOGN <= 12, WIDE = MODE == NTT_WIDE;
+    constexpr uint32_t PW = n + n / 16;
+    extern __shared__ uint32_t s[];                  // two of N + N/16 words, then (TW_LDS) the twiddles
     const uint32_t t = threadIdx.x;
     // the L limb blocks of a node, and consecutive nodes of a client, run on
     // one XCD: the node's digits and the client's RGSW rows stay in its L2
     const uint32_t lb = xcd_remap(blockIdx.x, gridDim.x);
     const uint32_t l = lb % L, node = lb / L;
     const uint32_t b = node / nout, tn = node % nout;
-    const uint32_t q = pr.q[l];
+    const uint32_t q = pr.q[l], qn = pr.qn[l];
     const uint64_t LN = (uint64_t)L * n;
     const uint32_t *c0 = ct + ((uint64_t)(b * 2) * ncols + 2 * tn) * LN + (uint64_t)l * n;   // component 0
     uint32_t *o = out + ((uint64_t)(b * 2) * nout + tn) * LN + (uint64_t)l * n;
@@ -382,10 +390,12 @@ coltor_mac_reg_kernel(const uint32_t *__restrict__ ct, const uint32_t *__restric
     }
     const ModQ &m = pr.mod[l];
     const uint32_t *tw = pr.fwd[l], *tws = tw + n;
-    uint2 *stw = reinterpret_cast<uint2 *>(s + n + n / 16);
+    uint2 w0[QR];
+    tw_first<LOGN>(w0, TwGlobal{WIDE ? tw : tw + 2 * n, tws});
+    uint32_t *stw = s + 2 * PW;
     if constexpr (TW_LDS) {
-        tw_pairs_fill<LOGN>(stw, tw, tws, t);
-        __syncthreads();
+        tw_lds_fill<LOGN, WIDE>(stw, tw, t);
+        lds_sync();
     }
     uint64_t acc[2][QR];
     uint32_t wraps[2][QR];
@@ -401,35 +411,48 @@ coltor_mac_reg_kernel(const uint32_t *__restrict__ ct, const uint32_t *__restric
     const uint32_t ne = 2 * ell;
     const int32_t *dg = digits + (uint64_t)node * ne * n + qf_elem(t, 0, LOGN - 4);
     int32_t dn[QR];
+    NttVal<MODE> v[QR];   // (low words stay zero across the transforms, see mont_bfly)
 #pragma unroll
-    for (int r = 0; r < QR; ++r) dn[r] = dg[qf_rpart(r, LOGN - 4)];
+    for (int r = 0; r < QR; ++r) dn[r] = dg[qf_rpart(r, LOGN - 4)], v[r] = 0;
     for (uint32_t pi = 0; pi < ne; ++pi) {
         const uint32_t p = pi >= ell, i = pi - p * ell;
-        uint32_t v[QR];
 #pragma unroll
-        for (int r = 0; r < QR; ++r) v[r] = dn[r] < 0 ? (uint32_t)(dn[r] + (int64_t)q) : (uint32_t)dn[r];
+        for (int r = 0; r < QR; ++r) ntt_set(v[r], dn[r] < 0 ? (uint32_t)dn[r] + q : (uint32_t)dn[r]);
         if (pi + 1 < ne) {
             dg += n;
 #pragma unroll
             for (int r = 0; r < QR; ++r) dn[r] = dg[qf_rpart(r, LOGN - 4)];
         }
-        if constexpr (TW_LDS) ntt_reg_block<LOGN, MODE>(v, t, s, TwPairsLds<LOGN>{stw}, q);
-        else ntt_reg_block<LOGN, MODE>(v, t, s, TwGlobal{tw, tws}, q);
+        // two buffers in turn: a wave that reaches the barrier of one transform
+        // has read its part of the one before
+        uint32_t *buf = s + (pi % 2) * PW;
         const uint4 *row = reinterpret_cast<const uint4 *>(
-            rgsw_p + ((((uint64_t)b * 2 + p) * ell + i) * 2) * LN + (uint64_t)l * n + (uint64_t)t * QR);
+                               rgsw_p + ((((uint64_t)b * 2 + p) * ell + i) * 2) * LN + (uint64_t)l * n) + t;
+        // the row's first component is loaded before the last butterflies, the
+        // second before the first's products (loaded vector by vector at their
+        // products they cost eight L2 latencies a digit)
+        uint4 w4[2][QR / 4];
+        auto load_row = [&](int c) {
+#pragma unroll
+            for (int g = 0; g < QR / 4; ++g) w4[c][g] = row[c * (LN / 4) + g * T];
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto first = [&] { load_row(0); };
+        if constexpr (TW_LDS) ntt_reg_block<LOGN, MODE>(v, t, buf, w0, TwLds<LOGN, WIDE>{stw}, q, qn, first);
+        else ntt_reg_block<LOGN, MODE>(v, t, buf, w0, TwGlobal{WIDE ? tw : tw + 2 * n, tws}, q, qn, first);
+        load_row(1);
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const uint4 w4 = row[c * (LN / 4) + g];
-                const uint32_t w[4] = {w4.x, w4.y, w4.z, w4.w};
+            for (int g = 0; g < QR / 4; ++g) {
+                const uint32_t w[4] = {w4[c][g].x, w4[c][g].y, w4[c][g].z, w4[c][g].w};
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     const int r = 4 * g + k;
                     // NTT_GROW: the unreduced value (below (1 + 2 logN) q)
                     // goes into the 64-bit sum; the host checks 2 ell of
                     // these products fit
-                    const uint32_t x = MODE == NTT_LAZY ? qf_reduce4(v[r], q, 2 * q) : v[r];
+                    const uint32_t x = MODE == NTT_LAZY ? qf_reduce4(ntt_get(v[r]), q, 2 * q) : ntt_get(v[r]);
                     if (MODE == NTT_WIDE) mad_wide(acc[c][r], wraps[c][r], x, w[k]);
                     else acc[c][r] += (uint64_t)x * w[k];
                 }
@@ -440,13 +463,14 @@ coltor_mac_reg_kernel(const uint32_t *__restrict__ ct, const uint32_t *__restric
     // output polynomial to natural order, then out = ct0 + sum
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-        __syncthreads();
+        lds_sync();
 #pragma unroll
         for (int r = 0; r < QR; ++r) {
-            const uint32_t res = MODE == NTT_WIDE ? reduce_wide(acc[c][r], wraps[c][r], m) : reduce64(acc[c][r], m);
+            const uint32_t res = MODE == NTT_WIDE ? reduce_wide(acc[c][r], wraps[c][r], m)
+                                                  : mont_reduce<MODE == NTT_GROW>(acc[c][r], m.r64, pr.r1[l], q, qn);
             s[qf_pad(__brev(t * QR) >> (32 - LOGN)) + qf_pad(__brev((uint32_t)r) >> (32 - LOGN))] = res;
         }
-        __syncthreads();
+        lds_sync();
 #pragma unroll
         for (int r = 0; r < QR; ++r) {
             const uint32_t j = t + r * T;
@@ -504,6 +528,8 @@ void launch_coltor_stage(const pir_params &ring, const uint32_t *ct, uint32_t B,
         pr.fwd[l] = t.fwd;
         pr.inv[l] = t.inv;
         pr.q[l] = q;
+        pr.qn[l] = t.qn;
+        pr.r1[l] = (uint32_t)((1ull << 32) / q);
         pr.ninv[l] = t.n_inv;
         pr.ninv_s[l] = t.n_inv_shoup;
         const u128 qh = Q / q;
@@ -563,7 +589,7 @@ void launch_coltor_stage(const pir_params &ring, const uint32_t *ct, uint32_t B,
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_p));
         rgsw_permute_kernel<<<(uint32_t)(rg_words / n), 256, lds_p, st>>>(rgsw, rgp.as<uint32_t>(), logn);
         PIR_LAUNCH_CHECK();
-        const size_t lds = (size_t)(n + n / 16) * sizeof(uint32_t) + (logn <= 12 ? (size_t)n * sizeof(uint2) : 0);
+        const size_t lds = ((size_t)2 * (n + n / 16) + (logn <= 12 ? wide ? 2 * n : n : 0)) * sizeof(uint32_t);
         auto go2 = [&](auto kern) {
             PIR_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
@@ -571,11 +597,13 @@ void launch_coltor_stage(const pir_params &ring, const uint32_t *ct, uint32_t B,
                                                                pr);
         };
         // unreduced butterflies when every prime leaves room for logN stages of
-        // growth and 2 ell products of the grown values fit a 64-bit sum
+        // growth and 2 ell products of the grown values fit a 64-bit sum, with
+        // q 2^32 to spare (mont_reduce)
         bool grow = !wide;
         for (uint32_t l = 0; l < L && grow; ++l) {
             const u128 bound = (u128)(1 + 2 * logn) * ring.q[l];
-            grow = bound < ((u128)1 << 32) && bound * ring.q[l] * (2 * ell) < ((u128)1 << 64);
+            grow = bound < ((u128)1 << 32) &&
+                   bound * ring.q[l] * (2 * ell) + ((u128)ring.q[l] << 32) < ((u128)1 << 64);
         }
         auto pick = [&](auto mode) {
             constexpr int M = decltype(mode)::value;

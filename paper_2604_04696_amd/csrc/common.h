@@ -94,9 +94,12 @@ uint32_t pow_mod(uint64_t a, uint64_t e, uint32_t q);
 // Tables for the on-device negacyclic NTT of one prime.
 struct NttTables {
     uint32_t q = 0, n = 0;
-    uint32_t *fwd = nullptr;      // [n] psi^brv(i) and Shoup companions [n]
+    // [n] psi^brv(i), [n] Shoup companions, [n] Montgomery forms w 2^32 mod q,
+    // and the three once more in the order of tw_slot (n >= 256)
+    uint32_t *fwd = nullptr;
     uint32_t *inv = nullptr;      // [n] psi^-brv(i) and companions [n]
     uint32_t n_inv = 0, n_inv_shoup = 0;
+    uint32_t qn = 0;              // -q^-1 mod 2^32
 };
 
 // Tables are built once per (q, n) and kept for the process lifetime.

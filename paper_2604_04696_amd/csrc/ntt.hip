@@ -14,12 +14,11 @@
 //   N >= 256  register-blocked (nttreg.h): N/16 threads hold 16 values each,
 //             up to four butterfly stages per LDS exchange;
 //   N < 256   one LDS stage per barrier, eight polynomials per block.
-// The register-blocked form is bound by VALU issue (about ten instructions per
+// The register-blocked form is bound by VALU issue (seven instructions per
 // butterfly) with the memory traffic, one read and one write, close behind.
-// On 1 GiB (65536 polynomials, N = 4096) it takes 0.50-0.64 ms; one LDS stage
-// per barrier, one launch per limb, took 2.04 ms, and the same transform in
-// blocks of 1024 threads (four polynomials) 0.54 ms on the 1 GiB query where
-// it now takes 0.50 ms.
+// On 1 GiB (65536 polynomials, N = 4096) it takes 0.45-0.47 ms; with Shoup's
+// butterflies and barriers at every exchange 0.49-0.50 ms; one LDS stage per
+// barrier, one launch per limb, 2.04 ms.
 //
 // Writing the MFMA path's digit planes straight from the transform (8 bytes of
 // each 64-byte plane row per block) was measured and is not used: those
@@ -96,32 +95,48 @@ const NttTables &ntt_tables(uint32_t q, uint32_t n) {
     uint32_t psi_inv = pow_mod(psi, q - 2, q);
     if (pow_mod(psi, n, q) != q - 1)
         PIR_FAIL(PIR_EINVAL, "psi is not a primitive 2N-th root mod %u", q);
-    std::vector<uint32_t> fwd(2 * n), inv(2 * n);
+    std::vector<uint32_t> fwd(6 * n), inv(2 * n);
     for (uint32_t k = 0; k < n; ++k) {
         uint32_t e = bitrev(k, logn);
         fwd[k] = pow_mod(psi, e, q);
         fwd[n + k] = shoup(fwd[k], q);
+        fwd[2 * n + k] = (uint32_t)(((uint64_t)fwd[k] << 32) % q);
         inv[k] = pow_mod(psi_inv, e, q);
         inv[n + k] = shoup(inv[k], q);
+    }
+    for (uint32_t k = 0; k < n; ++k) {
+        // the slot of tw_slot: group k is of stage x = logn - 1 - floor(log2 k)
+        uint32_t at = k;
+        const uint32_t T = n / 16;
+        if (n >= 256 && k >= T) {
+            uint32_t base = T, sh = 0;
+            while (2 * base <= k) base *= 2, ++sh;
+            at = base + ((k - base) & ((1u << sh) - 1)) * T + ((k - base) >> sh);
+        }
+        for (uint32_t part = 0; part < 3; ++part) fwd[(3 + part) * n + at] = fwd[part * n + k];
     }
     NttTables t;
     t.q = q;
     t.n = n;
-    t.fwd = static_cast<uint32_t *>(dev_alloc(sizeof(uint32_t) * 2 * n));
+    t.fwd = static_cast<uint32_t *>(dev_alloc(sizeof(uint32_t) * 6 * n));
     t.inv = static_cast<uint32_t *>(dev_alloc(sizeof(uint32_t) * 2 * n));
-    PIR_HIP(hipMemcpy(t.fwd, fwd.data(), sizeof(uint32_t) * 2 * n, hipMemcpyHostToDevice));
+    PIR_HIP(hipMemcpy(t.fwd, fwd.data(), sizeof(uint32_t) * 6 * n, hipMemcpyHostToDevice));
     PIR_HIP(hipMemcpy(t.inv, inv.data(), sizeof(uint32_t) * 2 * n, hipMemcpyHostToDevice));
     t.n_inv = pow_mod(n, q - 2, q);
     t.n_inv_shoup = shoup(t.n_inv, q);
+    uint32_t qi = q;   // Newton's iteration for q^-1 mod 2^32 (q q = 1 mod 8 for odd q)
+    for (int i = 0; i < 4; ++i) qi *= 2 - q * qi;
+    t.qn = 0u - qi;
     return cache.emplace(key, t).first->second;
 }
 
 // ------------------------------------------------------------------ kernels
 struct NttPrimes {
-    const uint32_t *tw[PIR_MAX_PRIMES];   // twiddles of the direction: [n] powers, [n] Shoup companions
+    const uint32_t *tw[PIR_MAX_PRIMES];   // twiddles of the direction: [n] powers, [n] Shoup companions, forward also [n] Montgomery forms
     uint32_t q[PIR_MAX_PRIMES];
     uint32_t r1[PIR_MAX_PRIMES];          // floor(2^32 / q): Shoup companion of 1
     uint32_t ninv[PIR_MAX_PRIMES], ninv_s[PIR_MAX_PRIMES];
+    uint32_t qn[PIR_MAX_PRIMES];          // -q^-1 mod 2^32
 };
 
 // Polynomials of a block: block b takes limb b % L of records
@@ -203,8 +218,8 @@ ntt_reg_kernel(const uint32_t *in, uint32_t *out, uint32_t records, uint32_t L, 
     // x mod q + q, in [0, 2q) as the lazy butterflies allow (for q >= 2^30,
     // canonical, with 64-bit intermediates).  The forward transform's first
     // stage pairs registers r and r + 8, and only its first operands need the
-    // reduction: the second ones go into Shoup's product, which takes any
-    // 32-bit value.
+    // reduction: the second ones go into the butterfly's product, which takes
+    // any 32-bit value.
     uint32_t v[QR];
 #pragma unroll
     for (int r = 0; r < QR; ++r) {
@@ -231,15 +246,22 @@ ntt_reg_kernel(const uint32_t *in, uint32_t *out, uint32_t records, uint32_t L, 
         for (int r = 0; r < QR; ++r)
             if (live) out[off + t + r * T] = WIDE ? mul_shoup_w(v[r], ni, nis, q) : mul_shoup(v[r], ni, nis, q);
     } else {
-        ntt_reg_block<LOGN, WIDE ? NTT_WIDE : NTT_LAZY>(v, t, poly, TwGlobal{tw, tws}, q);
+        constexpr int MODE = WIDE ? NTT_WIDE : NTT_LAZY;
+        NttVal<MODE> x[QR];
+#pragma unroll
+        for (int r = 0; r < QR; ++r) x[r] = 0, ntt_set(x[r], v[r]);
+        const TwGlobal src{WIDE ? tw : tw + 2 * n, tws};
+        uint2 w0[QR];
+        tw_first<LOGN>(w0, src);
+        ntt_reg_block<LOGN, MODE>(x, t, poly, w0, src, q, pr.qn[l], [] {});
         // element 16t + r holds point bitrev(16t + r): natural order through
         // LDS, then coalesced stores
-        __syncthreads();
+        lds_sync();
         const uint32_t pb = qf_pad(__brev(t * QR) >> (32 - LOGN));
 #pragma unroll
         for (int r = 0; r < QR; ++r)
-            poly[pb + qf_pad(__brev((uint32_t)r) >> (32 - LOGN))] = WIDE ? v[r] : qf_reduce4(v[r], q, 2 * q);
-        __syncthreads();
+            poly[pb + qf_pad(__brev((uint32_t)r) >> (32 - LOGN))] = WIDE ? ntt_get(x[r]) : qf_reduce4(ntt_get(x[r]), q, 2 * q);
+        lds_sync();
 #pragma unroll
         for (int r = 0; r < QR; ++r)
             if (live) out[off + t + r * T] = poly[qf_pad(t) + qf_pad(r * T)];
@@ -260,6 +282,7 @@ void launch_ntt(const uint32_t *in, uint32_t *out, uint64_t records, uint32_t n,
         pr.r1[l] = (uint32_t)((1ull << 32) / q[l]);
         pr.ninv[l] = t.n_inv;
         pr.ninv_s[l] = t.n_inv_shoup;
+        pr.qn[l] = t.qn;
         wide = wide || q[l] >= WIDE_Q;
     }
     // gridDim.x is limited to 2^31 - 1: at most 2^28 records of four limbs a launch
