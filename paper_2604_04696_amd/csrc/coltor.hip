@@ -21,7 +21,11 @@
 //                      reconstruction and decomposition, coefficient by
 //                      coefficient; digits go out as int32 [node][2][ell][N]
 //                      (ell*N words per polynomial instead of L*N residues
-//                      per digit: each limb reduces them on load);
+//                      per digit: each limb reduces them on load).  8192
+//                      nodes at N = 4096, four limbs, ell = 5: 0.76-0.88 ms;
+//                      with Gentleman-Sande butterflies, all limbs at once in
+//                      blocks of 1024 threads, and 128-bit sums and
+//                      comparisons per coefficient 0.95-1.1 ms;
 //   multiply-accumulate one block per (node, limb): for each of the 2*ell
 //                      digit polynomials, the residues mod q_l, the forward
 //                      NTT and the product with the two RGSW components of
@@ -54,7 +58,7 @@ constexpr int CT_THREADS = 512;
 
 struct ColtorPrimes {
     const uint32_t *fwd[PIR_MAX_PRIMES];   // forward twiddles [n] + Shoup companions [n] + Montgomery forms [n] + LDS order (NttTables)
-    const uint32_t *inv[PIR_MAX_PRIMES];   // inverse twiddles [n] + companions [n]
+    const uint32_t *inv[PIR_MAX_PRIMES];   // inverse twiddles (NttTables)
     uint32_t q[PIR_MAX_PRIMES], qn[PIR_MAX_PRIMES];        // the primes and -q^-1 mod 2^32
     uint32_t r1[PIR_MAX_PRIMES];                           // floor(2^32 / q)
     uint32_t ninv[PIR_MAX_PRIMES], ninv_s[PIR_MAX_PRIMES];
@@ -64,9 +68,10 @@ struct ColtorPrimes {
     ModQ mod[PIR_MAX_PRIMES];
     uint32_t qhat[PIR_MAX_PRIMES][4];                          // Q/q_l, 32-bit limbs, low first
     uint32_t Q[4], Qhalf[4];                                   // Q and floor(Q/2)
+    uint32_t crt_cm[PIR_MAX_PRIMES];                           // crt_cn in Montgomery form
     // the short form (Q < 2^125 and log2z * ell <= 126): C = sum_{i < ell-1} (z/2) z^i
-    // and C - Q mod 2^128, and 1/q_l in binary64
-    uint32_t C[4], CmQ[4];
+    // and 1/q_l in binary64
+    uint32_t C[4], nQ[4];                                      // (nQ: -Q mod 2^128)
     double qinv[PIR_MAX_PRIMES];
     uint32_t fast;
 };
@@ -144,62 +149,16 @@ coltor_dcp_kernel(const uint32_t *__restrict__ ct, uint32_t ncols, uint32_t nout
 }
 
 // ------------------------------- kernel 1, register-blocked (N >= 256)
-// L*N/16 threads: thread group l (N/16 threads) transforms limb l with 16
-// values per thread, then all limbs of a coefficient meet in LDS for the
-// reconstruction.  Shared by the decomposition: (Q/q_l)^-1 N^-1 mod q_l.
-// The short form: y_l = x_l (Q/q_l)^-1 N^-1 mod q_l; S = sum_l y_l Q/q_l taken
-// mod 2^128 and k = floor(sum_l y_l / q_l) in binary64 (S - k Q is the
-// reconstruction up to one Q either way: the estimate's error is far below 1,
-// and S - k Q lies in (-Q, 2Q), inside the signed 128-bit range for
-// Q < 2^125).  The balanced digits of the centred value v are the plain
-// base-z digits of v + C, each less z/2 (C = sum_{i < ell-1} (z/2) z^i: adding
-// z/2 to each digit position is what the balanced recursion's rounding does),
-// and the last one is what remains after ell-1 arithmetic shifts; the value
-// stays below 2^126 since log2z * ell <= 126.  Digit i is then one mask of the
-// low word and a 4-word funnel shift.
-__device__ __forceinline__ void dcp_coefficient_short(const uint32_t *x, uint32_t L, uint32_t j, uint32_t log2z,
-                                                      uint32_t ell, uint64_t n, int32_t *dst,
-                                                      const ColtorPrimes &pr, bool wide) {
-    const u128 Q = u128_of(pr.Q);
-    u128 S = 0;
-    double fk = 0.0;
-    for (uint32_t l = 0; l < L; ++l) {
-        const uint32_t q = pr.q[l];
-        const uint32_t y = wide ? mul_shoup_w(x[l], pr.crt_cn[l], pr.crt_cns[l], q)
-                                : mul_shoup(x[l], pr.crt_cn[l], pr.crt_cns[l], q);
-        fk = fma((double)y, pr.qinv[l], fk);
-        S += (u128)y * u128_of(pr.qhat[l]);
-    }
-    u128 v = S - (u128)(uint32_t)fk * Q;
-    if ((i128)v < 0) v += Q;
-    else if (v >= Q) v -= Q;
-    v += v > u128_of(pr.Qhalf) ? u128_of(pr.CmQ) : u128_of(pr.C);
-    uint32_t w0 = (uint32_t)v, w1 = (uint32_t)(v >> 32), w2 = (uint32_t)(v >> 64), w3 = (uint32_t)(v >> 96);
-    const uint32_t zmask = (1u << log2z) - 1, zhalf = 1u << (log2z - 1);
-    for (uint32_t i = 0; i + 1 < ell; ++i) {
-        dst[i * n + j] = (int32_t)(w0 & zmask) - (int32_t)zhalf;
-        w0 = __builtin_amdgcn_alignbit(w1, w0, log2z);
-        w1 = __builtin_amdgcn_alignbit(w2, w1, log2z);
-        w2 = __builtin_amdgcn_alignbit(w3, w2, log2z);
-        w3 = (uint32_t)((int32_t)w3 >> log2z);
-    }
-    dst[(ell - 1) * n + j] = (int32_t)w0;
-}
-
-__device__ __forceinline__ void dcp_coefficient(const uint32_t *x, uint32_t L, uint32_t j, uint32_t log2z,
-                                                uint32_t ell, uint64_t n, int32_t *dst, const ColtorPrimes &pr,
-                                                bool wide) {
-    if (pr.fast) {
-        dcp_coefficient_short(x, L, j, log2z, ell, n, dst, pr, wide);
-        return;
-    }
+// The coefficient from y_l = x_l (Q/q_l)^-1 mod q_l, step by step.
+__device__ __forceinline__ void dcp_coefficient(const uint32_t (&y)[PIR_MAX_PRIMES], uint32_t L, uint32_t j,
+                                                uint32_t log2z, uint32_t ell, uint64_t n, int32_t *dst,
+                                                const ColtorPrimes &pr) {
     const u128 Q = u128_of(pr.Q), Qhalf = u128_of(pr.Qhalf);
     u128 acc = 0;
-    for (uint32_t l = 0; l < L; ++l) {
-        const uint32_t q = pr.q[l];
-        const uint32_t y = wide ? mul_shoup_w(x[l], pr.crt_cn[l], pr.crt_cns[l], q)
-                                : mul_shoup(x[l], pr.crt_cn[l], pr.crt_cns[l], q);
-        const u128 term = (u128)y * u128_of(pr.qhat[l]);
+#pragma unroll
+    for (uint32_t l = 0; l < PIR_MAX_PRIMES; ++l) {
+        if (l >= L) break;
+        const u128 term = (u128)y[l] * u128_of(pr.qhat[l]);
         u128 sum = acc + term;
         if (sum < acc || sum >= Q) sum -= Q;
         acc = sum;
@@ -215,44 +174,134 @@ __device__ __forceinline__ void dcp_coefficient(const uint32_t *x, uint32_t L, u
     dst[(ell - 1) * n + j] = (int32_t)v;
 }
 
-template <int LOGN, bool WIDE>
-__global__ void __launch_bounds__(1024)
-coltor_dcp_reg_kernel(const uint32_t *__restrict__ ct, uint32_t ncols, uint32_t nout, uint32_t L,
+// The short form: S = sum_l y_l Q/q_l and k = round(sum_l y_l / q_l) in
+// binary64, so that v = S - k Q is the centred value itself, unless the sum's
+// fraction is within 2^-40 of 1/2 (its error is below 2^-49): then the steps
+// above decide.  The balanced digits of v are the plain base-z digits of v + C,
+// each less z/2 (C = sum_{i < ell-1} (z/2) z^i: adding z/2 to each digit
+// position is what the balanced recursion's rounding does), and the last one is
+// what remains after ell-1 arithmetic shifts; the value stays below 2^126 since
+// log2z * ell <= 126.  v + C is formed mod 2^128 in four columns of 32-bit
+// words, each a 64-bit sum of C, k (-Q) and the L products (NARROW: every q is
+// below 2^30, as N >= 256 primes are by at least 2 N - 1, so a column with the
+// carry into it stays below 4 (2^30 - 512) (2^32 - 1) + 4 (2^32 - 1) + 2^33 <
+// 2^64), and digit i is one mask of the low word and a 4-word funnel shift.
+template <bool NARROW>
+__device__ __forceinline__ void dcp_coefficient_short(const uint32_t (&y)[PIR_MAX_PRIMES], uint32_t L, uint32_t j,
+                                                      uint32_t log2z, uint32_t ell, uint32_t n, int32_t *dst,
+                                                      const ColtorPrimes &pr) {
+    double fk = 0.5;
+#pragma unroll
+    for (uint32_t l = 0; l < PIR_MAX_PRIMES; ++l)
+        if (l < L) fk = fma((double)y[l], pr.qinv[l], fk);
+    const double kf = floor(fk), fr = fk - kf;
+    if (fr < 0x1p-40 || fr > 1.0 - 0x1p-40) {
+        dcp_coefficient(y, L, j, log2z, ell, n, dst, pr);
+        return;
+    }
+    const uint32_t k = (uint32_t)kf;
+    uint32_t w0, w1, w2, w3;
+    if (NARROW) {
+        uint64_t c[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) c[i] = (uint64_t)k * pr.nQ[i] + pr.C[i];
+#pragma unroll
+        for (uint32_t l = 0; l < PIR_MAX_PRIMES; ++l) {
+            if (l >= L) break;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) c[i] += (uint64_t)y[l] * pr.qhat[l][i];
+        }
+        w0 = (uint32_t)c[0];
+        c[1] += c[0] >> 32;
+        w1 = (uint32_t)c[1];
+        c[2] += c[1] >> 32;
+        w2 = (uint32_t)c[2];
+        w3 = (uint32_t)c[3] + (uint32_t)(c[2] >> 32);
+    } else {
+        u128 v = u128_of(pr.C) + (u128)k * u128_of(pr.nQ);
+#pragma unroll
+        for (uint32_t l = 0; l < PIR_MAX_PRIMES; ++l)
+            if (l < L) v += (u128)y[l] * u128_of(pr.qhat[l]);
+        w0 = (uint32_t)v, w1 = (uint32_t)(v >> 32), w2 = (uint32_t)(v >> 64), w3 = (uint32_t)(v >> 96);
+    }
+    const uint32_t zmask = (1u << log2z) - 1, zhalf = 1u << (log2z - 1);
+    for (uint32_t i = 0; i + 1 < ell; ++i) {
+        (dst + i * n)[j] = (int32_t)(w0 & zmask) - (int32_t)zhalf;
+        w0 = __builtin_amdgcn_alignbit(w1, w0, log2z);
+        w1 = __builtin_amdgcn_alignbit(w2, w1, log2z);
+        w2 = __builtin_amdgcn_alignbit(w3, w2, log2z);
+        w3 = (uint32_t)((int32_t)w3 >> log2z);
+    }
+    (dst + (ell - 1) * n)[j] = (int32_t)w0;
+}
+
+// A block transforms G limbs at a time (N/16 threads each, 16 values per
+// thread), all L one after the other into LDS, where the limbs of a coefficient
+// meet for the reconstruction.
+template <int LOGN, int MODE>
+__global__ void __launch_bounds__((1u << LOGN) / QR <= 512 ? 512 : 1024)
+coltor_dcp_reg_kernel(const uint32_t *__restrict__ ct, uint32_t ncols, uint32_t nout, uint32_t L, uint32_t G,
                       uint32_t log2z, uint32_t ell, int32_t *__restrict__ digits, ColtorPrimes pr) {
     constexpr uint32_t n = 1u << LOGN, T = n / QR, PW = n + n / 16;
     extern __shared__ uint32_t s[];                  // [L][PW]
-    const uint32_t tid = threadIdx.x, l = tid / T, t = tid % T;
+    const uint32_t tid = threadIdx.x, g = tid / T, t = tid % T;
     const uint32_t p = blockIdx.x % 2, node = blockIdx.x / 2;
     const uint32_t b = node / nout, tn = node % nout;
     if (2 * tn + 1 >= ncols) return;                 // unpaired column: no product
     const uint64_t LN = (uint64_t)L * n;
-    const uint32_t *c0 = ct + ((uint64_t)(b * 2 + p) * ncols + 2 * tn) * LN + (uint64_t)l * n;
-    const uint32_t *c1 = c0 + LN;
-    const uint32_t q = pr.q[l];
-    uint32_t *poly = s + l * PW;
+    const uint32_t *col = ct + ((uint64_t)(b * 2 + p) * ncols + 2 * tn) * LN;
 
-    // difference; point j goes to position bitrev(j)
+    for (uint32_t l0 = 0; l0 < L; l0 += G) {         // (G divides L)
+        const uint32_t l = l0 + (T >= 64 ? __builtin_amdgcn_readfirstlane(g) : g);
+        const uint32_t q = pr.q[l];
+        const uint32_t *c0 = col + (uint64_t)l * n, *c1 = c0 + LN;
+        uint32_t *poly = s + l * PW;
+        // difference; point j goes to position bitrev(j)
 #pragma unroll
-    for (int r = 0; r < QR; ++r) {
-        // t < T = 2^(LOGN-4): t and r T are disjoint bit fields (see qf_rpart)
-        const uint32_t j = t + r * T;
-        poly[qf_pad(__brev(t) >> (32 - LOGN)) + qf_pad(__brev((uint32_t)r * T) >> (32 - LOGN))] =
-            sub_mod(c1[j], c0[j], q);
+        for (int r = 0; r < QR; ++r) {
+            // t < T = 2^(LOGN-4): t and r T are disjoint bit fields (see qf_rpart)
+            poly[qf_pad(__brev(t) >> (32 - LOGN)) + qf_pad(__brev((uint32_t)r * T) >> (32 - LOGN))] =
+                sub_mod((c1 + r * T)[t], (c0 + r * T)[t], q);
+        }
+        lds_sync();
+        const uint32_t pe = qf_pad(qf_elem(t, 0, LOGN - 4));
+        if constexpr (MODE == NTT_WIDE) {
+            uint32_t v[QR];
+#pragma unroll
+            for (int r = 0; r < QR; ++r) v[r] = poly[qf_pad(t * QR) + r];
+            intt_reg_block<LOGN, true>(v, t, poly, pr.inv[l], pr.inv[l] + n, q);
+            lds_sync();
+#pragma unroll
+            for (int r = 0; r < QR; ++r)
+                poly[pe + qf_pad(qf_rpart(r, LOGN - 4))] = mul_shoup_w(v[r], pr.crt_cn[l], pr.crt_cns[l], q);
+        } else {
+            const uint32_t qn = pr.qn[l], cm = pr.crt_cm[l];
+            uint64_t v[QR];
+#pragma unroll
+            for (int r = 0; r < QR; ++r) v[r] = (uint64_t)poly[qf_pad(t * QR) + r] << 32;
+            uint32_t psi[QR];   // psi^-i of the thread's results, there when they are
+#pragma unroll
+            for (int r = 0; r < QR; ++r) psi[r] = (pr.inv[l] + 3 * n + r * T)[t];
+            __builtin_amdgcn_sched_barrier(0);
+            intt_dit_block<LOGN, MODE>(v, t, poly, pr.inv[l] + 2 * n, q, qn);
+            // times psi^-i, N^-1 and (Q/q_l)^-1; to where the last exchange was
+            // read from, which no other thread reads
+            if (LOGN <= 10) lds_wave_order();
+#pragma unroll
+            for (int r = 0; r < QR; ++r) {
+                const uint32_t x = mont_mul(mont_mul(hi32(v[r]), psi[r], q, qn), cm, q, qn);
+                poly[pe + qf_pad(qf_rpart(r, LOGN - 4))] = min(x, x - q);
+            }
+        }
     }
-    __syncthreads();
-    uint32_t v[QR];
-#pragma unroll
-    for (int r = 0; r < QR; ++r) v[r] = poly[qf_pad(t * QR) + r];
-    intt_reg_block<LOGN, WIDE>(v, t, poly, pr.inv[l], pr.inv[l] + n, q);
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < QR; ++r) poly[qf_pad(qf_elem(t, 0, LOGN - 4)) + qf_pad(qf_rpart(r, LOGN - 4))] = v[r];
-    __syncthreads();
+    lds_sync();
     int32_t *dst = digits + ((uint64_t)node * 2 + p) * ell * n;
-    for (uint32_t j = tid; j < n; j += L * T) {
-        uint32_t x[PIR_MAX_PRIMES];
-        for (uint32_t k = 0; k < L; ++k) x[k] = s[k * PW + qf_pad(j)];
-        dcp_coefficient(x, L, j, log2z, ell, n, dst, pr, WIDE);
+    for (uint32_t j = tid; j < n; j += G * T) {
+        uint32_t y[PIR_MAX_PRIMES];
+#pragma unroll
+        for (uint32_t k = 0; k < PIR_MAX_PRIMES; ++k) y[k] = k < L ? s[k * PW + qf_pad(j)] : 0;
+        if (pr.fast) dcp_coefficient_short<MODE != NTT_WIDE>(y, L, j, log2z, ell, n, dst, pr);
+        else dcp_coefficient(y, L, j, log2z, ell, n, dst, pr);
     }
 }
 
@@ -520,7 +569,7 @@ void launch_coltor_stage(const pir_params &ring, const uint32_t *ct, uint32_t B,
         u128 C = 0, zi = 1;
         for (uint32_t i = 0; i + 1 < ell; ++i, zi <<= log2z) C += zi << (log2z - 1);
         split128(C, pr.C);
-        split128(C - Q, pr.CmQ);
+        split128(-Q, pr.nQ);
     }
     for (uint32_t l = 0; l < L; ++l) {
         const uint32_t q = ring.q[l];
@@ -539,6 +588,7 @@ void launch_coltor_stage(const pir_params &ring, const uint32_t *ct, uint32_t B,
         pr.crt_cs[l] = shoup32(c, q);
         pr.crt_cn[l] = (uint32_t)((uint64_t)c * t.n_inv % q);
         pr.crt_cns[l] = shoup32(pr.crt_cn[l], q);
+        pr.crt_cm[l] = (uint32_t)(((uint64_t)pr.crt_cn[l] << 32) % q);
         pr.mod[l] = make_modq(q);
         pr.qinv[l] = 1.0 / (double)q;
         pr.mu[l] = pr.mod[l].mu;
@@ -550,27 +600,42 @@ void launch_coltor_stage(const pir_params &ring, const uint32_t *ct, uint32_t B,
     StreamScratch scratch((size_t)nodes * 2 * ell * n * sizeof(int32_t), st);
     int32_t *dg = scratch.as<int32_t>();
 
+    // unreduced butterflies when every prime leaves room for logN stages of
+    // growth and 2 ell products of the grown values fit a 64-bit sum, with
+    // q 2^32 to spare (mont_reduce)
+    bool grow = !wide;
+    for (uint32_t l = 0; l < L && grow; ++l) {
+        const u128 bound = (u128)(1 + 2 * logn) * ring.q[l];
+        grow = bound < ((u128)1 << 32) && bound * ring.q[l] * (2 * ell) + ((u128)ring.q[l] << 32) < ((u128)1 << 64);
+    }
     if (n >= 256) {
         const size_t lds = (size_t)L * (n + n / 16) * sizeof(uint32_t);
+        // limbs at a time: a divisor of L, blocks of up to 512 threads (two on
+        // a CU with the registers that the transforms want)
+        const uint32_t T = n / QR;
+        uint32_t G = 1;
+        for (uint32_t d = 2; d <= L; ++d)
+            if (L % d == 0 && d * T <= 512) G = d;
         auto go1 = [&](auto kern) {
             PIR_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-            kern<<<(uint32_t)(nodes * 2), L * (n / QR), lds, st>>>(ct, ncols, nout, L, log2z, ell, dg, pr);
+            kern<<<(uint32_t)(nodes * 2), G * T, lds, st>>>(ct, ncols, nout, L, G, log2z, ell, dg, pr);
         };
-        auto pick1 = [&](auto w) {
-            constexpr bool W = decltype(w)::value;
+        auto pick1 = [&](auto mode) {
+            constexpr int M = decltype(mode)::value;
             switch (logn) {
-                case 8: go1(&coltor_dcp_reg_kernel<8, W>); break;
-                case 9: go1(&coltor_dcp_reg_kernel<9, W>); break;
-                case 10: go1(&coltor_dcp_reg_kernel<10, W>); break;
-                case 11: go1(&coltor_dcp_reg_kernel<11, W>); break;
-                case 12: go1(&coltor_dcp_reg_kernel<12, W>); break;
-                case 13: go1(&coltor_dcp_reg_kernel<13, W>); break;
-                default: go1(&coltor_dcp_reg_kernel<14, W>); break;
+                case 8: go1(&coltor_dcp_reg_kernel<8, M>); break;
+                case 9: go1(&coltor_dcp_reg_kernel<9, M>); break;
+                case 10: go1(&coltor_dcp_reg_kernel<10, M>); break;
+                case 11: go1(&coltor_dcp_reg_kernel<11, M>); break;
+                case 12: go1(&coltor_dcp_reg_kernel<12, M>); break;
+                case 13: go1(&coltor_dcp_reg_kernel<13, M>); break;
+                default: go1(&coltor_dcp_reg_kernel<14, M>); break;
             }
         };
-        if (wide) pick1(std::true_type{});
-        else pick1(std::false_type{});
+        if (wide) pick1(std::integral_constant<int, NTT_WIDE>{});
+        else if (grow) pick1(std::integral_constant<int, NTT_GROW>{});
+        else pick1(std::integral_constant<int, NTT_LAZY>{});
     } else {
         const size_t lds1 = (size_t)L * n * sizeof(uint32_t);
         PIR_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&coltor_dcp_kernel),
@@ -596,15 +661,6 @@ void launch_coltor_stage(const pir_params &ring, const uint32_t *ct, uint32_t B,
             kern<<<(uint32_t)(nodes * L), n / QR, lds, st>>>(ct, rgp.as<uint32_t>(), dg, out, ncols, nout, L, ell,
                                                                pr);
         };
-        // unreduced butterflies when every prime leaves room for logN stages of
-        // growth and 2 ell products of the grown values fit a 64-bit sum, with
-        // q 2^32 to spare (mont_reduce)
-        bool grow = !wide;
-        for (uint32_t l = 0; l < L && grow; ++l) {
-            const u128 bound = (u128)(1 + 2 * logn) * ring.q[l];
-            grow = bound < ((u128)1 << 32) &&
-                   bound * ring.q[l] * (2 * ell) + ((u128)ring.q[l] << 32) < ((u128)1 << 64);
-        }
         auto pick = [&](auto mode) {
             constexpr int M = decltype(mode)::value;
             switch (logn) {

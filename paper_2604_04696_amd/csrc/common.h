@@ -97,7 +97,9 @@ struct NttTables {
     // [n] psi^brv(i), [n] Shoup companions, [n] Montgomery forms w 2^32 mod q,
     // and the three once more in the order of tw_slot (n >= 256)
     uint32_t *fwd = nullptr;
-    uint32_t *inv = nullptr;      // [n] psi^-brv(i) and companions [n]
+    // [n] psi^-brv(i), [n] companions; in Montgomery form [n] the powers of
+    // intt_dit_block and [n] psi^-i
+    uint32_t *inv = nullptr;
     uint32_t n_inv = 0, n_inv_shoup = 0;
     uint32_t qn = 0;              // -q^-1 mod 2^32
 };

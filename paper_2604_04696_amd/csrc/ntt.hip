@@ -95,7 +95,7 @@ const NttTables &ntt_tables(uint32_t q, uint32_t n) {
     uint32_t psi_inv = pow_mod(psi, q - 2, q);
     if (pow_mod(psi, n, q) != q - 1)
         PIR_FAIL(PIR_EINVAL, "psi is not a primitive 2N-th root mod %u", q);
-    std::vector<uint32_t> fwd(6 * n), inv(2 * n);
+    std::vector<uint32_t> fwd(6 * n), inv(4 * n);
     for (uint32_t k = 0; k < n; ++k) {
         uint32_t e = bitrev(k, logn);
         fwd[k] = pow_mod(psi, e, q);
@@ -104,6 +104,13 @@ const NttTables &ntt_tables(uint32_t q, uint32_t n) {
         inv[k] = pow_mod(psi_inv, e, q);
         inv[n + k] = shoup(inv[k], q);
     }
+    for (uint32_t s = 0; (1u << s) < n; ++s) {
+        const uint64_t w = pow_mod(psi_inv, 2ull * (n >> (s + 1)), q);
+        uint64_t x = (1ull << 32) % q;
+        for (uint32_t k = 0; k < 1u << s; ++k, x = x * w % q) inv[2 * n + (1u << s) + k] = (uint32_t)x;
+    }
+    uint64_t y = (1ull << 32) % q;
+    for (uint32_t i = 0; i < n; ++i, y = y * psi_inv % q) inv[3 * n + i] = (uint32_t)y;
     for (uint32_t k = 0; k < n; ++k) {
         // the slot of tw_slot: group k is of stage x = logn - 1 - floor(log2 k)
         uint32_t at = k;
@@ -119,9 +126,9 @@ const NttTables &ntt_tables(uint32_t q, uint32_t n) {
     t.q = q;
     t.n = n;
     t.fwd = static_cast<uint32_t *>(dev_alloc(sizeof(uint32_t) * 6 * n));
-    t.inv = static_cast<uint32_t *>(dev_alloc(sizeof(uint32_t) * 2 * n));
+    t.inv = static_cast<uint32_t *>(dev_alloc(sizeof(uint32_t) * 4 * n));
     PIR_HIP(hipMemcpy(t.fwd, fwd.data(), sizeof(uint32_t) * 6 * n, hipMemcpyHostToDevice));
-    PIR_HIP(hipMemcpy(t.inv, inv.data(), sizeof(uint32_t) * 2 * n, hipMemcpyHostToDevice));
+    PIR_HIP(hipMemcpy(t.inv, inv.data(), sizeof(uint32_t) * 4 * n, hipMemcpyHostToDevice));
     t.n_inv = pow_mod(n, q - 2, q);
     t.n_inv_shoup = shoup(t.n_inv, q);
     uint32_t qi = q;   // Newton's iteration for q^-1 mod 2^32 (q q = 1 mod 8 for odd q)

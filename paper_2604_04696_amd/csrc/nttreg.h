@@ -71,6 +71,12 @@ __device__ __forceinline__ uint32_t mont_reduce(uint64_t x, uint32_t r64, uint32
     return min(w, w - q);
 }
 
+// x w mod q in [0, 2q), w in Montgomery form, any 32-bit x.
+__device__ __forceinline__ uint32_t mont_mul(uint32_t x, uint32_t w, uint32_t q, uint32_t qn) {
+    const uint64_t p = (uint64_t)x * w;
+    return hi32((uint64_t)((uint32_t)p * qn) * q + p);
+}
+
 // [0, 4q) -> [0, q)
 __device__ __forceinline__ uint32_t qf_reduce4(uint32_t x, uint32_t q, uint32_t q2) {
     x = min(x, x - q2);
@@ -225,6 +231,65 @@ __device__ __forceinline__ void ntt_reg_block(NttVal<MODE> (&v)[QR], uint32_t t,
                 } else {
                     if (MODE == NTT_LAZY) v[r] = with_hi(v[r], min(hi32(v[r]), hi32(v[r]) - 2 * q));
                     mont_bfly(v[r], v[r | bit], w2.x, q, qn);
+                }
+            }
+        }
+    }
+}
+
+// Inverse transform by decimation in time, with the butterfly of the forward
+// one: the plain discrete Fourier transform of bit-reversed input, whose first
+// two stages need no product for the power 1, and the powers of psi^-1 left to
+// the caller's scaling (merged into Gentleman-Sande butterflies, whose sums
+// need a correction of their own, they take eight instructions a butterfly).
+// On entry register r of thread t holds position 16t + r of the bit-reversed
+// arrangement (point bitrev(16t + r)), a residue below q; on return N psi^i
+// times coefficient i = qf_elem(t, r, LOGN - 4), bounded as for
+// ntt_reg_block.  w: Montgomery forms of omega^-(k N / 2^(s+1)) at 2^s + k for
+// stage s, k < 2^s (omega = psi^2).  poly as for intt_reg_block.
+template <int LOGN, int MODE>
+__device__ __forceinline__ void intt_dit_block(uint64_t (&v)[QR], uint32_t t, uint32_t *poly, const uint32_t *w,
+                                               uint32_t q, uint32_t qn) {
+    static_assert(MODE != NTT_WIDE, "");
+    int lo = 0;
+#pragma unroll
+    for (int clo = 0; clo < LOGN; clo += 4) {
+        const int chi = clo + 4 < LOGN ? clo + 4 : LOGN;
+        const int rlo = clo < LOGN - 4 ? clo : LOGN - 4;   // registers cover [rlo, rlo + 4)
+        uint32_t tw[QR];   // stage rlo + b: the power of registers = k mod 2^b at 2^b - 1 + k
+        const uint32_t tl = t & ((1u << rlo) - 1);
+#pragma unroll
+        for (int s = clo; s < chi; ++s) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (k < 1 << (s - rlo)) tw[(1 << (s - rlo)) - 1 + k] = (w + (1u << s) + ((uint32_t)k << rlo))[tl];
+        }
+        if (rlo != lo) {
+            if (lo > 6) lds_sync();   // the other waves have read what this one overwrites
+            else lds_wave_order();
+            const uint32_t pw = qf_pad(qf_elem(t, 0, lo)), pr = qf_pad(qf_elem(t, 0, rlo));
+#pragma unroll
+            for (int r = 0; r < QR; ++r) poly[pw + qf_pad(qf_rpart(r, lo))] = hi32(v[r]);
+            if (rlo > 6) lds_sync();
+            else lds_wave_order();
+#pragma unroll
+            for (int r = 0; r < QR; ++r) v[r] = with_hi(v[r], poly[pr + qf_pad(qf_rpart(r, rlo))]);
+            lo = rlo;
+        }
+#pragma unroll
+        for (int s = clo; s < chi; ++s) {
+            const int b = s - rlo, bit = 1 << b;
+#pragma unroll
+            for (int r = 0; r < QR; ++r) {
+                if (r & bit) continue;
+                const int k = r & (bit - 1);
+                if (s < 2 && k == 0) {   // power 1, values below 2q
+                    const uint32_t x = hi32(v[r]), y = hi32(v[r | bit]);
+                    v[r] = with_hi(v[r], x + y);
+                    v[r | bit] = with_hi(v[r | bit], x - y + (s + 1) * q);
+                } else {
+                    if (MODE == NTT_LAZY) v[r] = with_hi(v[r], min(hi32(v[r]), hi32(v[r]) - 2 * q));
+                    mont_bfly(v[r], v[r | bit], tw[bit - 1 + k], q, qn);
                 }
             }
         }
