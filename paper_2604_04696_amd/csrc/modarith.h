@@ -77,6 +77,26 @@ __device__ __forceinline__ void mad_wide(uint64_t &sum, uint32_t &wraps, uint32_
     sum = t;
 }
 
+// Four of them, x the same for every lane of the wave: the carry out of
+// v_mad_u64_u32 is added to the wraps, two instructions a product.  (From
+// __builtin_add_overflow the compiler makes four: multiply, add, compare, add.)
+// A carry is read three instructions after it is written; gfx950 wants two.
+__device__ __forceinline__ void mad_wide4(uint64_t (&sum)[4], uint32_t (&wraps)[4], const uint4 &x, const uint4 &y) {
+    uint64_t c0, c1, c2, c3;
+    asm("v_mad_u64_u32 %0, %8, %12, %16, %0\n\t"
+        "v_mad_u64_u32 %1, %9, %13, %17, %1\n\t"
+        "v_mad_u64_u32 %2, %10, %14, %18, %2\n\t"
+        "v_mad_u64_u32 %3, %11, %15, %19, %3\n\t"
+        "v_addc_co_u32 %4, vcc, 0, %4, %8\n\t"
+        "v_addc_co_u32 %5, vcc, 0, %5, %9\n\t"
+        "v_addc_co_u32 %6, vcc, 0, %6, %10\n\t"
+        "v_addc_co_u32 %7, vcc, 0, %7, %11"
+        : "+v"(sum[0]), "+v"(sum[1]), "+v"(sum[2]), "+v"(sum[3]), "+v"(wraps[0]), "+v"(wraps[1]), "+v"(wraps[2]),
+          "+v"(wraps[3]), "=&s"(c0), "=&s"(c1), "=&s"(c2), "=&s"(c3)
+        : "s"(x.x), "s"(x.y), "s"(x.z), "s"(x.w), "v"(y.x), "v"(y.y), "v"(y.z), "v"(y.w)
+        : "vcc");
+}
+
 // Shoup multiplication by a constant w < q with companion ws = floor(w*2^32/q):
 // a*w - floor(a*ws/2^32)*q lies in [0, 2q) for a < 2^32; one correction.
 __device__ __forceinline__ uint32_t mul_shoup(uint32_t a, uint32_t w, uint32_t ws, uint32_t q) {
