@@ -43,6 +43,7 @@
 // (64-bit intermediates) for any prime of 2^30 or more, lazy below, and
 // unreduced forward butterflies when (1 + 2 logN) q < 2^32; the small-ring
 // forms use the wide arithmetic throughout.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -239,7 +240,7 @@ __device__ __forceinline__ void dcp_coefficient_short(const uint32_t (&y)[PIR_MA
 // thread), all L one after the other into LDS, where the limbs of a coefficient
 // meet for the reconstruction.
 template <int LOGN, int MODE>
-__global__ void __launch_bounds__((1u << LOGN) / QR <= 512 ? 512 : 1024)
+__global__ void __launch_bounds__(1024)
 coltor_dcp_reg_kernel(const uint32_t *__restrict__ ct, uint32_t ncols, uint32_t nout, uint32_t L, uint32_t G,
                       uint32_t log2z, uint32_t ell, int32_t *__restrict__ digits, ColtorPrimes pr) {
     constexpr uint32_t n = 1u << LOGN, T = n / QR, PW = n + n / 16;
@@ -407,11 +408,19 @@ rgsw_permute_kernel(const uint32_t *__restrict__ in, uint32_t *__restrict__ out,
     }
 }
 
-template <int LOGN, int MODE>
+// SPLIT: where the nodes leave CUs idle (fewer than 256 (node, limb) blocks: a
+// tournament of one client has 64 nodes and fewer in seven of nine stages, one
+// block of ten transforms takes 26 us, ten of one transform 7 us and their sum
+// 6-7 us; with 32 nodes, four parts, 20 and 6 us), a (node, limb) is split into `parts`
+// blocks of digit polynomials; `rgsw_p` then holds the rows as given (gathered:
+// a few digits a block cost less than the permuting launch), and the block's
+// sums go to `out` as [part][node][limb][2][N] residues in the transform's
+// order, for coltor_sum_kernel to add up.
+template <int LOGN, int MODE, bool SPLIT>
 __global__ void __launch_bounds__((1u << LOGN) / QR)
 coltor_mac_reg_kernel(const uint32_t *__restrict__ ct, const uint32_t *__restrict__ rgsw_p,
                       const int32_t *__restrict__ digits, uint32_t *__restrict__ out, uint32_t ncols,
-                      uint32_t nout, uint32_t L, uint32_t ell, ColtorPrimes pr) {
+                      uint32_t nout, uint32_t L, uint32_t ell, uint32_t parts, ColtorPrimes pr) {
     constexpr uint32_t n = 1u << LOGN, T = n / QR;
     // up to N = 4096 the twiddles are staged in LDS: kept in registers across
     // the 2 ell transforms they took ~90 VGPRs
@@ -421,7 +430,9 @@ coltor_mac_reg_kernel(const uint32_t *__restrict__ ct, const uint32_t *__restric
     const uint32_t t = threadIdx.x;
     // the L limb blocks of a node, and consecutive nodes of a client, run on
     // one XCD: the node's digits and the client's RGSW rows stay in its L2
-    const uint32_t lb = xcd_remap(blockIdx.x, gridDim.x);
+    uint32_t lb = xcd_remap(blockIdx.x, gridDim.x);
+    const uint32_t part = SPLIT ? lb % parts : 0;
+    if (SPLIT) lb /= parts;
     const uint32_t l = lb % L, node = lb / L;
     const uint32_t b = node / nout, tn = node % nout;
     const uint32_t q = pr.q[l], qn = pr.qn[l];
@@ -431,6 +442,7 @@ coltor_mac_reg_kernel(const uint32_t *__restrict__ ct, const uint32_t *__restric
     const uint64_t c_in = (uint64_t)ncols * LN, c_out = (uint64_t)nout * LN;   // component strides
 
     if (2 * tn + 1 >= ncols) {                       // unpaired column passes through
+        if (SPLIT) return;
 #pragma unroll
         for (int c = 0; c < 2; ++c)
 #pragma unroll
@@ -453,17 +465,18 @@ coltor_mac_reg_kernel(const uint32_t *__restrict__ ct, const uint32_t *__restric
 #pragma unroll
         for (int r = 0; r < QR; ++r) acc[c][r] = 0, wraps[c][r] = 0;
 
-    // the 2 ell digit polynomials of the node (p, i) in turn; the next one's
+    // the 2 ell digit polynomials of the node (p, i) in turn (a part's share of
+    // them, at most one more than another's); the next one's
     // values are loaded while the current one is transformed (waiting for
     // them right before each transform left the SIMDs idle for a third of
     // the kernel)
-    const uint32_t ne = 2 * ell;
-    const int32_t *dg = digits + (uint64_t)node * ne * n + qf_elem(t, 0, LOGN - 4);
+    const uint32_t pi0 = SPLIT ? part * (2 * ell) / parts : 0, ne = SPLIT ? (part + 1) * (2 * ell) / parts : 2 * ell;
+    const int32_t *dg = digits + ((uint64_t)node * (2 * ell) + pi0) * n + qf_elem(t, 0, LOGN - 4);
     int32_t dn[QR];
     NttVal<MODE> v[QR];   // (low words stay zero across the transforms, see mont_bfly)
 #pragma unroll
     for (int r = 0; r < QR; ++r) dn[r] = dg[qf_rpart(r, LOGN - 4)], v[r] = 0;
-    for (uint32_t pi = 0; pi < ne; ++pi) {
+    for (uint32_t pi = pi0; pi < ne; ++pi) {
         const uint32_t p = pi >= ell, i = pi - p * ell;
 #pragma unroll
         for (int r = 0; r < QR; ++r) ntt_set(v[r], dn[r] < 0 ? (uint32_t)dn[r] + q : (uint32_t)dn[r]);
@@ -475,15 +488,23 @@ coltor_mac_reg_kernel(const uint32_t *__restrict__ ct, const uint32_t *__restric
         // two buffers in turn: a wave that reaches the barrier of one transform
         // has read its part of the one before
         uint32_t *buf = s + (pi % 2) * PW;
-        const uint4 *row = reinterpret_cast<const uint4 *>(
-                               rgsw_p + ((((uint64_t)b * 2 + p) * ell + i) * 2) * LN + (uint64_t)l * n) + t;
+        const uint32_t *row1 = rgsw_p + ((((uint64_t)b * 2 + p) * ell + i) * 2) * LN + (uint64_t)l * n;
+        const uint4 *row = reinterpret_cast<const uint4 *>(row1) + t;
         // the row's first component is loaded before the last butterflies, the
         // second before the first's products (loaded vector by vector at their
         // products they cost eight L2 latencies a digit)
         uint4 w4[2][QR / 4];
         auto load_row = [&](int c) {
 #pragma unroll
-            for (int g = 0; g < QR / 4; ++g) w4[c][g] = row[c * (LN / 4) + g * T];
+            for (int g = 0; g < QR / 4; ++g) {
+                if constexpr (SPLIT) {   // points bitrev(16t + r)
+                    const uint32_t *at = row1 + c * LN + (__brev(t * QR) >> (32 - LOGN));
+                    auto r = [](int k) { return __builtin_bitreverse32((uint32_t)k) >> (32 - LOGN); };
+                    w4[c][g] = make_uint4(at[r(4 * g)], at[r(4 * g + 1)], at[r(4 * g + 2)], at[r(4 * g + 3)]);
+                } else {
+                    w4[c][g] = row[c * (LN / 4) + g * T];
+                }
+            }
             __builtin_amdgcn_sched_barrier(0);
         };
         auto first = [&] { load_row(0); };
@@ -508,6 +529,21 @@ coltor_mac_reg_kernel(const uint32_t *__restrict__ ct, const uint32_t *__restric
             }
         }
     }
+    auto result = [&](int c, int r) {
+        return MODE == NTT_WIDE ? reduce_wide(acc[c][r], wraps[c][r], m)
+                                : mont_reduce<MODE == NTT_GROW>(acc[c][r], m.r64, pr.r1[l], q, qn);
+    };
+    if constexpr (SPLIT) {
+        const uint64_t nodes = gridDim.x / (parts * L);
+        uint4 *to = reinterpret_cast<uint4 *>(out + (((part * nodes + node) * L + l) * 2) * n) + t;
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int g = 0; g < QR / 4; ++g)
+                to[c * (n / 4) + g * T] =
+                    make_uint4(result(c, 4 * g), result(c, 4 * g + 1), result(c, 4 * g + 2), result(c, 4 * g + 3));
+        return;
+    }
     // register r of thread t holds point bitrev(16t + r): one exchange per
     // output polynomial to natural order, then out = ct0 + sum
 #pragma unroll
@@ -515,9 +551,7 @@ coltor_mac_reg_kernel(const uint32_t *__restrict__ ct, const uint32_t *__restric
         lds_sync();
 #pragma unroll
         for (int r = 0; r < QR; ++r) {
-            const uint32_t res = MODE == NTT_WIDE ? reduce_wide(acc[c][r], wraps[c][r], m)
-                                                  : mont_reduce<MODE == NTT_GROW>(acc[c][r], m.r64, pr.r1[l], q, qn);
-            s[qf_pad(__brev(t * QR) >> (32 - LOGN)) + qf_pad(__brev((uint32_t)r) >> (32 - LOGN))] = res;
+            s[qf_pad(__brev(t * QR) >> (32 - LOGN)) + qf_pad(__brev((uint32_t)r) >> (32 - LOGN))] = result(c, r);
         }
         lds_sync();
 #pragma unroll
@@ -526,6 +560,52 @@ coltor_mac_reg_kernel(const uint32_t *__restrict__ ct, const uint32_t *__restric
             o[c * c_out + j] = add_mod_w(c0[c * c_in + j], s[qf_pad(t) + qf_pad(r * T)], q);
         }
     }
+}
+
+// Adds the partial sums of SPLIT blocks to ct0.  grid: nodes * L * 2 blocks, one
+// polynomial (node, limb, component) each; word 4 (g N/16 + t) + k of a partial
+// sum is point bitrev(16t + 4g + k).  A matter of latency: a thread has one
+// vector (four for N = 16384) of every part, eight loads at a time in flight.
+constexpr uint32_t SUM_THREADS = 1024;
+
+__global__ void __launch_bounds__(SUM_THREADS)
+coltor_sum_kernel(const uint32_t *__restrict__ ct, const uint4 *__restrict__ sums, uint32_t *__restrict__ out,
+                  uint32_t ncols, uint32_t nout, uint32_t L, uint32_t logn, uint32_t parts, ColtorPrimes pr) {
+    extern __shared__ uint32_t s[];   // n + n/64 words
+    const uint32_t n = 1u << logn, T = n / QR;
+    const uint32_t c = blockIdx.x % 2, l = blockIdx.x / 2 % L, node = blockIdx.x / 2 / L;
+    const uint32_t b = node / nout, tn = node % nout, q = pr.q[l];
+    const uint64_t part = (uint64_t)gridDim.x * (n / 4);   // vectors between parts
+    const uint4 *p0 = sums + (uint64_t)blockIdx.x * (n / 4);
+    const uint32_t *c0 = ct + ((((uint64_t)b * 2 + c) * ncols + 2 * tn) * L + l) * n;
+    uint32_t *o = out + ((((uint64_t)b * 2 + c) * nout + tn) * L + l) * n;
+    const bool paired = 2 * tn + 1 < ncols;
+    if (paired) {
+        for (uint32_t e = threadIdx.x; e < n / 4; e += blockDim.x) {
+            uint32_t x[4] = {0, 0, 0, 0};
+            for (uint32_t k0 = 0; k0 < parts; k0 += 8) {
+                uint4 v[8];
+#pragma unroll
+                for (uint32_t k = 0; k < 8; ++k) v[k] = p0[min(k0 + k, parts - 1) * part + e];
+#pragma unroll
+                for (uint32_t k = 0; k < 8; ++k) {
+                    if (k0 + k >= parts) break;
+                    x[0] = add_mod_w(x[0], v[k].x, q);
+                    x[1] = add_mod_w(x[1], v[k].y, q);
+                    x[2] = add_mod_w(x[2], v[k].z, q);
+                    x[3] = add_mod_w(x[3], v[k].w, q);
+                }
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k) {
+                const uint32_t j = e % T * QR + e / T * 4 + k, at = __brev(j) >> (32 - logn);
+                s[at + (at >> 6)] = x[k];
+            }
+        }
+    }
+    __syncthreads();
+    for (uint32_t j = threadIdx.x; j < n; j += blockDim.x)
+        o[j] = paired ? add_mod_w(c0[j], s[j + (j >> 6)], q) : c0[j];
 }
 
 // ------------------------------------------------------------------ host
@@ -552,6 +632,9 @@ void coltor_check_gadget(const pir_params &ring, uint32_t log2z, uint32_t ell) {
         PIR_FAIL(PIR_EUNSUPPORTED, "the stage keeps L*N = %u words in LDS; at most 16384",
                  ring.n * ring.nprimes);
 }
+
+// Blocks that keep the CUs busy (two each).
+constexpr uint64_t SPLIT_BLOCKS = 512;
 
 void launch_coltor_stage(const pir_params &ring, const uint32_t *ct, uint32_t B, uint32_t ncols,
                          const uint32_t *rgsw, uint32_t log2z, uint32_t ell, uint32_t *out, hipStream_t st) {
@@ -611,11 +694,12 @@ void launch_coltor_stage(const pir_params &ring, const uint32_t *ct, uint32_t B,
     if (n >= 256) {
         const size_t lds = (size_t)L * (n + n / 16) * sizeof(uint32_t);
         // limbs at a time: a divisor of L, blocks of up to 512 threads (two on
-        // a CU with the registers that the transforms want)
+        // a CU with the registers that the transforms want), up to 1024 where
+        // there is no second block for a CU
         const uint32_t T = n / QR;
         uint32_t G = 1;
         for (uint32_t d = 2; d <= L; ++d)
-            if (L % d == 0 && d * T <= 512) G = d;
+            if (L % d == 0 && d * T <= (nodes * 2 <= SPLIT_BLOCKS / 2 ? 1024 : 512)) G = d;
         auto go1 = [&](auto kern) {
             PIR_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
@@ -645,38 +729,57 @@ void launch_coltor_stage(const pir_params &ring, const uint32_t *ct, uint32_t B,
     }
     PIR_LAUNCH_CHECK();
     if (n >= 256) {
-        // RGSW rows in the transform's register order, then the blocked kernel
+        // with idle CUs: the digit polynomials of a (node, limb) in several
+        // blocks, else the RGSW rows in the transform's register order, then
+        // one block each
+        const uint32_t most = (uint32_t)(SPLIT_BLOCKS / (nodes * L)), per = most ? (2 * ell + most - 1) / most : 2 * ell;
+        const uint32_t parts = (2 * ell + per - 1) / per;
+        const bool split = parts > 1;
         const uint64_t rg_words = (uint64_t)B * 4 * ell * L * n;
         PIR_REQUIRE(rg_words / 256 < (1ull << 31), "ColTor launch too large");
-        StreamScratch rgp(rg_words * sizeof(uint32_t), st);
+        StreamScratch tmp((split ? parts * nodes * L * 2 * n : rg_words) * sizeof(uint32_t), st);
         const size_t lds_p = (size_t)(n + n / 64) * sizeof(uint32_t);
-        PIR_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&rgsw_permute_kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_p));
-        rgsw_permute_kernel<<<(uint32_t)(rg_words / n), 256, lds_p, st>>>(rgsw, rgp.as<uint32_t>(), logn);
-        PIR_LAUNCH_CHECK();
+        if (!split) {
+            PIR_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&rgsw_permute_kernel),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_p));
+            rgsw_permute_kernel<<<(uint32_t)(rg_words / n), 256, lds_p, st>>>(rgsw, tmp.as<uint32_t>(), logn);
+            PIR_LAUNCH_CHECK();
+        }
         const size_t lds = ((size_t)2 * (n + n / 16) + (logn <= 12 ? wide ? 2 * n : n : 0)) * sizeof(uint32_t);
-        auto go2 = [&](auto kern) {
+        auto go = [&](auto kern) {
             PIR_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-            kern<<<(uint32_t)(nodes * L), n / QR, lds, st>>>(ct, rgp.as<uint32_t>(), dg, out, ncols, nout, L, ell,
-                                                               pr);
+            kern<<<(uint32_t)(nodes * L * (split ? parts : 1)), n / QR, lds, st>>>(
+                ct, split ? rgsw : tmp.as<uint32_t>(), dg, split ? tmp.as<uint32_t>() : out, ncols, nout, L, ell, parts,
+                pr);
         };
         auto pick = [&](auto mode) {
             constexpr int M = decltype(mode)::value;
+            auto both = [&](auto lg) {
+                if (split) go(&coltor_mac_reg_kernel<decltype(lg)::value, M, true>);
+                else go(&coltor_mac_reg_kernel<decltype(lg)::value, M, false>);
+            };
             switch (logn) {
-                case 8: go2(&coltor_mac_reg_kernel<8, M>); break;
-                case 9: go2(&coltor_mac_reg_kernel<9, M>); break;
-                case 10: go2(&coltor_mac_reg_kernel<10, M>); break;
-                case 11: go2(&coltor_mac_reg_kernel<11, M>); break;
-                case 12: go2(&coltor_mac_reg_kernel<12, M>); break;
-                case 13: go2(&coltor_mac_reg_kernel<13, M>); break;
-                default: go2(&coltor_mac_reg_kernel<14, M>); break;
+                case 8: both(std::integral_constant<int, 8>{}); break;
+                case 9: both(std::integral_constant<int, 9>{}); break;
+                case 10: both(std::integral_constant<int, 10>{}); break;
+                case 11: both(std::integral_constant<int, 11>{}); break;
+                case 12: both(std::integral_constant<int, 12>{}); break;
+                case 13: both(std::integral_constant<int, 13>{}); break;
+                default: both(std::integral_constant<int, 14>{}); break;
             }
         };
         if (wide) pick(std::integral_constant<int, NTT_WIDE>{});
         else if (grow) pick(std::integral_constant<int, NTT_GROW>{});
         else pick(std::integral_constant<int, NTT_LAZY>{});
         PIR_LAUNCH_CHECK();
+        if (split) {
+            PIR_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&coltor_sum_kernel),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_p));
+            coltor_sum_kernel<<<(uint32_t)(nodes * L * 2), std::min(SUM_THREADS, n / 4), lds_p, st>>>(
+                ct, tmp.as<uint4>(), out, ncols, nout, L, logn, parts, pr);
+            PIR_LAUNCH_CHECK();
+        }
         return;
     }
     const size_t lds2 = (size_t)n * sizeof(uint32_t);
