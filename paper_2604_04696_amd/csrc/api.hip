@@ -515,7 +515,16 @@ pir_status pir_db_load_ntt(pir_db *db, const uint32_t *src, uint32_t row0, uint3
             if (db->layouts & PIR_LAYOUT_MFMA) launch_db_layout_mfma(*db, src, row0, nrows, st);
             return;
         }
-        // coefficient domain: NTT into a stream-ordered temporary, in row chunks
+        // coefficient domain, a VALU layout and whole 64-row chunks of the
+        // digit planes: the transform writes the one, the other is made from it
+        const bool mfma = db->layouts & PIR_LAYOUT_MFMA, valu = db->layouts & PIR_LAYOUT_VALU;
+        const bool whole = row0 % 64 == 0 && ((row0 + nrows) % 64 == 0 || row0 + nrows == p.d0) &&
+                           p.nprimes * (p.n / 4ull) * ((p.d1 + 63) / 64) * (nrows / 64 + 1) < (1ull << 31);
+        if (valu && (!mfma || whole) && launch_ntt_layout_valu(*db, src, row0, nrows, st)) {
+            if (mfma) launch_db_planes_from_valu(*db, row0, nrows, st);
+            return;
+        }
+        // else NTT into a stream-ordered temporary, in row chunks
         // of at most ~1 GiB, then build the layouts from it
         const uint32_t chunk = (uint32_t)std::max<uint64_t>(1, (1ull << 30) / (row_words * 4));
         const uint32_t rows_tmp = std::min(chunk, nrows);

@@ -228,6 +228,12 @@ void launch_ntt(const uint32_t *in, uint32_t *out, uint64_t records, uint32_t n,
                 bool inverse, hipStream_t st);
 void launch_db_layout_valu(const pir_db &db, const uint32_t *ntt_src, uint32_t row0,
                            uint32_t nrows, hipStream_t st);
+// Coefficients straight into the VALU layout; false (nothing enqueued) where
+// another way has to be taken.
+bool launch_ntt_layout_valu(const pir_db &db, const uint32_t *src, uint32_t row0, uint32_t nrows, hipStream_t st);
+// The digit planes of DB rows [row0, row0 + nrows) from the VALU layout; row0 a
+// multiple of 64, the end too or D0.
+void launch_db_planes_from_valu(const pir_db &db, uint32_t row0, uint32_t nrows, hipStream_t st);
 void launch_db_layout_mfma(const pir_db &db, const uint32_t *ntt_src, uint32_t row0,
                            uint32_t nrows, hipStream_t st);
 void launch_rowsel_valu(const pir_db &db, const uint32_t *q, uint32_t B, uint32_t *out,

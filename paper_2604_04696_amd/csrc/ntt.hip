@@ -329,6 +329,116 @@ void launch_ntt(const uint32_t *in, uint32_t *out, uint64_t records, uint32_t n,
     }
 }
 
+// ------------------------------------------- transform into the VALU layout
+// Coefficients [nrows][D1][L][N] -> the VALU layout, with no NTT-domain copy in
+// between: a block transforms LB_C consecutive columns of one row and limb into
+// LDS (N/16 threads each) and writes 64-byte runs (LB_C columns of a point
+// group), whose other half the next block, on the same XCD, brings to the same
+// L2 line (64 registers: two blocks on a CU).  1 GiB of coefficients takes
+// 0.56 ms (as a transform and a layout
+// pass, which move twice the bytes, 0.45 and 0.37 ms); two columns a block
+// 0.80 ms, two after the other in blocks of 512 threads 0.57-0.60 ms,
+// non-temporal stores 0.66 ms.
+constexpr uint32_t LB_C = 4;
+static_assert(VALU_STRIP % LB_C == 0, "a block's columns lie in one strip");
+
+template <int LOGN>
+struct NttLayoutShape {
+    static constexpr uint32_t n = 1u << LOGN, T = n / QR;
+    static constexpr uint32_t THREADS = LB_C * T;
+    static constexpr uint32_t PW = n + n / 16 + 1;   // (+ 1: the columns of a group in distinct banks)
+};
+
+template <int LOGN, bool WIDE>
+__global__ void __launch_bounds__(NttLayoutShape<LOGN>::THREADS, 8)
+ntt_layout_valu_kernel(const uint32_t *__restrict__ in, uint4 *__restrict__ dst, uint32_t row0, uint32_t d0,
+                       uint32_t d1, uint32_t L, uint32_t nblk_n, NttPrimes pr) {
+    using S = NttLayoutShape<LOGN>;
+    constexpr uint32_t n = S::n, T = S::T;
+    constexpr int MODE = WIDE ? NTT_WIDE : NTT_LAZY;
+    extern __shared__ uint32_t s[];   // [LB_C][PW]
+    const uint32_t t = threadIdx.x % T, pi = threadIdx.x / T;
+    uint32_t b = xcd_remap(blockIdx.x, gridDim.x);
+    const uint32_t n0 = b % nblk_n * LB_C;
+    b /= nblk_n;
+    const uint32_t l = b % L, row = b / L;
+    const uint32_t q = pr.q[l], r1 = pr.r1[l];
+    const TwGlobal src{WIDE ? pr.tw[l] : pr.tw[l] + 2 * n, pr.tw[l] + n};
+    uint2 w0[QR];
+    tw_first<LOGN>(w0, src);
+    const uint32_t col = min(n0 + pi, d1 - 1);   // (columns past D1: not written)
+    const uint32_t *from = in + (((uint64_t)row * d1 + col) * L + l) * n;
+    uint32_t *poly = s + pi * S::PW;
+    NttVal<MODE> v[QR];
+    // any 32-bit value, as in ntt_reg_kernel
+#pragma unroll
+    for (int r = 0; r < QR; ++r) {
+        const uint32_t x = __builtin_nontemporal_load(from + r * T + t);
+        v[r] = 0;
+        if (WIDE) {
+            const uint64_t y = (uint64_t)x - (uint64_t)__umulhi(x, r1) * q;
+            ntt_set(v[r], (uint32_t)(y >= q ? y - q : y));
+        } else {
+            ntt_set(v[r], r & 8 ? x : x - __umulhi(x, r1) * q);
+        }
+    }
+    ntt_reg_block<LOGN, MODE>(v, t, poly, w0, src, q, pr.qn[l], [] {});
+    lds_sync();
+    const uint32_t pb = qf_pad(__brev(t * QR) >> (32 - LOGN));
+#pragma unroll
+    for (int r = 0; r < QR; ++r)
+        poly[pb + qf_pad(__brev((uint32_t)r) >> (32 - LOGN))] =
+            WIDE ? ntt_get(v[r]) : qf_reduce4(ntt_get(v[r]), q, 2 * q);
+    lds_sync();
+    const uint32_t strip = n0 / VALU_STRIP, w = valu_strip_width(strip, d1), c = threadIdx.x % LB_C;
+    if (n0 + c >= d1) return;
+    uint4 *to = dst + (uint64_t)(row0 + row) * w + (n0 + c) % VALU_STRIP;
+    for (uint32_t g = threadIdx.x / LB_C; g < n / 4; g += S::THREADS / LB_C) {
+        const uint32_t *x = s + c * S::PW + qf_pad(4 * g);
+        to[valu_strip_base(l * (n / 4) + g, strip, d0, d1)] = make_uint4(x[0], x[1], x[2], x[3]);
+    }
+}
+
+bool launch_ntt_layout_valu(const pir_db &db, const uint32_t *src, uint32_t row0, uint32_t nrows, hipStream_t st) {
+    const auto &p = db.p;
+    if (p.n < 256 || p.n > 4096) return false;
+    const uint32_t nblk_n = (p.d1 + LB_C - 1) / LB_C, L = p.nprimes;
+    if ((uint64_t)nblk_n * L * nrows >= (1ull << 31)) return false;
+    NttPrimes pr{};
+    bool wide = false;
+    for (uint32_t l = 0; l < L; ++l) {
+        const NttTables &t = ntt_tables(p.q[l], p.n);
+        pr.tw[l] = t.fwd;
+        pr.q[l] = p.q[l];
+        pr.r1[l] = (uint32_t)((1ull << 32) / p.q[l]);
+        pr.qn[l] = t.qn;
+        wide = wide || p.q[l] >= WIDE_Q;
+    }
+    auto go = [&](auto lg, auto w) {
+        constexpr int LG = decltype(lg)::value;
+        using S = NttLayoutShape<LG>;
+        auto kern = &ntt_layout_valu_kernel<LG, decltype(w)::value>;
+        const size_t lds = LB_C * S::PW * sizeof(uint32_t);
+        PIR_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)lds));
+        kern<<<nblk_n * L * nrows, S::THREADS, lds, st>>>(src, reinterpret_cast<uint4 *>(db.valu.data), row0, p.d0, p.d1,
+                                                         L, nblk_n, pr);
+    };
+    auto pick = [&](auto w) {
+        switch (p.n) {
+            case 256: go(std::integral_constant<int, 8>{}, w); break;
+            case 512: go(std::integral_constant<int, 9>{}, w); break;
+            case 1024: go(std::integral_constant<int, 10>{}, w); break;
+            case 2048: go(std::integral_constant<int, 11>{}, w); break;
+            default: go(std::integral_constant<int, 12>{}, w); break;
+        }
+    };
+    if (wide) pick(std::true_type{});
+    else pick(std::false_type{});
+    PIR_LAUNCH_CHECK();
+    return true;
+}
+
 // ------------------------------------------------------------ DB layouts
 // NTT-domain source rows [nrows][D1][L*N/4] -> VALU layout [L*N/4][S][D0][W]
 // (16-byte vectors of four points, 256-column strips, see DbLayoutValu).

@@ -48,6 +48,38 @@ static_assert(VALU_STRIP % XCOLS == 0, "a unit's columns lie in one DB strip");
 
 __device__ __forceinline__ void xbarrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// Eight rows k = 8 wv .. + 7 of a chunk for one column (lane) and four points,
+// cut into digits, to LDS [point][digit][column][64 k]: the 16-byte piece c of
+// column n sits at c ^ ((n >> 1) & 3) (fragment reads free of bank conflicts).
+template <bool WIDE>
+__device__ __forceinline__ void cut_rows(int8_t *buf, const uint4 (&raw)[8], uint32_t lane, uint32_t wv, uint32_t q) {
+    int8_t *const to = buf + lane * XCH + ((wv / 2) ^ ((lane >> 1) & 3)) * 16 + (wv % 2) * 8;
+    auto transpose4 = [](uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, uint32_t (&o)[4]) {
+        const uint32_t a = __builtin_amdgcn_perm(w1, w0, 0x06020400u);   // w0.0 w1.0 w0.2 w1.2
+        const uint32_t c = __builtin_amdgcn_perm(w1, w0, 0x07030501u);   // w0.1 w1.1 w0.3 w1.3
+        const uint32_t e = __builtin_amdgcn_perm(w3, w2, 0x06020400u);
+        const uint32_t f = __builtin_amdgcn_perm(w3, w2, 0x07030501u);
+        o[0] = __builtin_amdgcn_perm(e, a, 0x05040100u);
+        o[1] = __builtin_amdgcn_perm(f, c, 0x05040100u);
+        o[2] = __builtin_amdgcn_perm(e, a, 0x07060302u);
+        o[3] = __builtin_amdgcn_perm(f, c, 0x07060302u);
+    };
+#pragma unroll
+    for (int pi = 0; pi < 4; ++pi) {
+        uint32_t w[8], lo[4], hi[4];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const uint32_t x = pi == 0 ? raw[i].x : pi == 1 ? raw[i].y : pi == 2 ? raw[i].z : raw[i].w;
+            w[i] = WIDE ? split_digits_window(x, q) : split_digits(x);
+        }
+        transpose4(w[0], w[1], w[2], w[3], lo);
+        transpose4(w[4], w[5], w[6], w[7], hi);
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+            *reinterpret_cast<uint2 *>(to + (pi * 4 + d) * (XCOLS * XCH)) = make_uint2(lo[d], hi[d]);
+    }
+}
+
 template <int RT, int MODE>
 __global__ void __launch_bounds__(64 * XWAVES) __attribute__((amdgpu_waves_per_eu(2, 2)))
 rowsel_mfma_valu_kernel(const MfmaJob J, const uint4 *__restrict__ db, uint32_t d0) {
@@ -111,36 +143,6 @@ rowsel_mfma_valu_kernel(const MfmaJob J, const uint4 *__restrict__ db, uint32_t 
         }
     };
 
-    // the chunk in raw, cut into digits, to LDS: the 16-byte piece c of column
-    // n sits at c ^ ((n >> 1) & 3) (fragment reads free of bank conflicts)
-    auto cut = [&](int8_t *buf, uint32_t q) {
-        int8_t *const to = buf + lane * XCH + ((wv / 2) ^ ((lane >> 1) & 3)) * 16 + (wv % 2) * 8;
-        auto transpose4 = [](uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, uint32_t (&o)[4]) {
-            const uint32_t a = __builtin_amdgcn_perm(w1, w0, 0x06020400u);   // w0.0 w1.0 w0.2 w1.2
-            const uint32_t c = __builtin_amdgcn_perm(w1, w0, 0x07030501u);   // w0.1 w1.1 w0.3 w1.3
-            const uint32_t e = __builtin_amdgcn_perm(w3, w2, 0x06020400u);
-            const uint32_t f = __builtin_amdgcn_perm(w3, w2, 0x07030501u);
-            o[0] = __builtin_amdgcn_perm(e, a, 0x05040100u);
-            o[1] = __builtin_amdgcn_perm(f, c, 0x05040100u);
-            o[2] = __builtin_amdgcn_perm(e, a, 0x07060302u);
-            o[3] = __builtin_amdgcn_perm(f, c, 0x07060302u);
-        };
-#pragma unroll
-        for (int pi = 0; pi < 4; ++pi) {
-            uint32_t w[8], lo[4], hi[4];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const uint32_t x = pi == 0 ? raw[i].x : pi == 1 ? raw[i].y : pi == 2 ? raw[i].z : raw[i].w;
-                w[i] = MODE == RECOMB_WIDE ? split_digits_window(x, q) : split_digits(x);
-            }
-            transpose4(w[0], w[1], w[2], w[3], lo);
-            transpose4(w[4], w[5], w[6], w[7], hi);
-#pragma unroll
-            for (int d = 0; d < 4; ++d)
-                *reinterpret_cast<uint2 *>(to + (pi * 4 + d) * (XCOLS * XCH)) = make_uint2(lo[d], hi[d]);
-        }
-    };
-
     i32x4 acc[7][NS];
     auto zero_acc = [&]() {
 #pragma unroll
@@ -196,7 +198,7 @@ rowsel_mfma_valu_kernel(const MfmaJob J, const uint4 *__restrict__ db, uint32_t 
         for (uint32_t kc = 0; kc < nkc; ++kc) {
             int8_t *const buf = lds + b * XBUF;
             b ^= 1;
-            cut(buf, J.q[cu.l].q);
+            cut_rows<MODE == RECOMB_WIDE>(buf, raw, lane, wv, J.q[cu.l].q);
             i32x4 a[4];
 #pragma unroll
             for (int d = 0; d < 4; ++d) a[d] = qn[d];
@@ -228,6 +230,37 @@ rowsel_mfma_valu_kernel(const MfmaJob J, const uint4 *__restrict__ db, uint32_t 
     }
 }
 
+// The digit planes [L*N][4][Kp/64][D1][64] of a DB from its VALU layout: a block
+// takes a point group, 64 columns and a 64-row chunk, 1 KiB runs in and 4 KiB
+// runs out; HBM-bound, 1 GiB in 0.36 ms (6.0 TB/s both ways).  grid: groups * nblk_n * chunks.
+template <bool WIDE>
+__global__ void __launch_bounds__(64 * XWAVES)
+planes_from_valu_kernel(const uint4 *__restrict__ db, int8_t *__restrict__ planes, uint32_t d0, uint32_t d1,
+                        uint32_t G, uint32_t nkc, uint32_t c0, uint32_t nblk_n, uint32_t nchunk, uint4 qs) {
+    __shared__ __attribute__((aligned(1024))) int8_t lds[XBUF];
+    const uint32_t tid = threadIdx.x, lane = tid % 64;
+    const uint32_t wv = __builtin_amdgcn_readfirstlane(tid / 64);
+    uint32_t b = blockIdx.x;
+    const uint32_t n0 = b % nblk_n * XCOLS;
+    b /= nblk_n;
+    const uint32_t chunk = c0 + b % nchunk, gg = b / nchunk, l = gg / G;
+    const uint32_t strip = n0 / VALU_STRIP, w = valu_strip_width(strip, d1);
+    const uint4 *col = db + valu_strip_base(gg, strip, d0, d1) + min(n0 % VALU_STRIP + lane, w - 1);
+    const uint32_t k0 = chunk * XCH + 8 * wv;
+    uint4 raw[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) raw[i] = k0 + i < d0 ? ld_nt(col + (uint64_t)(k0 + i) * w) : make_uint4(0, 0, 0, 0);
+    cut_rows<WIDE>(lds, raw, lane, wv, l == 0 ? qs.x : l == 1 ? qs.y : l == 2 ? qs.z : qs.w);
+    xbarrier();
+#pragma unroll
+    for (int j = 0; j < XBUF / 16 / (64 * XWAVES); ++j) {
+        const uint32_t e = tid + 64 * XWAVES * j, kq = e % 4, n = e / 4 % XCOLS, pd = e / (4 * XCOLS);
+        if (n0 + n >= d1) continue;
+        const uint4 x = *reinterpret_cast<const uint4 *>(lds + (pd * XCOLS + n) * XCH + (kq ^ ((n >> 1) & 3)) * 16);
+        st_nt(reinterpret_cast<uint4 *>(planes + (((16ull * gg + pd) * nkc + chunk) * d1 + n0 + n) * XCH + kq * 16), x);
+    }
+}
+
 int valu_cu_count() {
     static int cached = 0;
     if (!cached) {
@@ -239,6 +272,23 @@ int valu_cu_count() {
 }
 
 }  // namespace
+
+void launch_db_planes_from_valu(const pir_db &db, uint32_t row0, uint32_t nrows, hipStream_t st) {
+    const auto &p = db.p;
+    const uint32_t nkc = db.mfma.kp / XCH, c0 = row0 / XCH, nchunk = (row0 + nrows + XCH - 1) / XCH - c0;
+    const uint32_t nblk_n = (p.d1 + XCOLS - 1) / XCOLS;
+    const uint64_t blocks = (uint64_t)p.nprimes * (p.n / 4) * nblk_n * nchunk;
+    if (row0 % XCH || ((row0 + nrows) % XCH && row0 + nrows != p.d0) || blocks >= (1ull << 31))
+        PIR_FAIL(PIR_EINVAL, "rows [%u, %u) are no whole chunks", row0, row0 + nrows);
+    const uint4 qs = make_uint4(p.q[0], p.q[1], p.q[2], p.q[3]);
+    auto go = [&](auto kern) {
+        kern<<<(uint32_t)blocks, 64 * XWAVES, 0, st>>>(reinterpret_cast<const uint4 *>(db.valu.data), db.mfma.data, p.d0,
+                                                      p.d1, p.n / 4, nkc, c0, nblk_n, nchunk, qs);
+    };
+    if (db.wide) go(&planes_from_valu_kernel<true>);
+    else go(&planes_from_valu_kernel<false>);
+    PIR_LAUNCH_CHECK();
+}
 
 void launch_rowsel_mfma_valu(const pir_db &db, const uint32_t *q, uint32_t B, uint32_t *out, hipStream_t st) {
     // scratch: query digit planes [P][4][Kp/64][rows][64], then the output
