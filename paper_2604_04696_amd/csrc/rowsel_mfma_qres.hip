@@ -11,9 +11,9 @@
 // query digit with v_mfma_i32_16x16x64_i8, so a DB fragment feeds RS and a
 // query fragment RN MFMAs per digit pair.  Per 64-row chunk of k the block
 // copies the query chunk (four digits x BM rows) and the DB chunk into LDS
-// rings; with one row group of waves (units of 32 or 64 rows x 128 columns)
-// each wave loads its own 16 columns into a ring of its own, with several
-// (96 x 64 and 128 x 64 units) the block shares one DB ring, since every row
+// rings; with one row group of waves (units of 32 rows x 128 columns) each wave
+// loads its own 16 columns into a ring of its own, with several (64 x 128,
+// 96 x 64 and 128 x 64 units) the block shares one DB ring, since every row
 // group reads the same columns.  The 32 x 128 unit is kept for tuning and
 // grouped plans: with 32 rows it ties with the tiled kernel.  Every wave
 // holds seven class accumulators per sub-tile: 112 registers for the four
@@ -122,7 +122,9 @@ __device__ __forceinline__ QUnit decode_unit(uint32_t u, const MfmaJob &J, uint3
 //      the block at a barrier, after which the buffers read in step t - 1
 //      are free;
 //   2. issues its loads of query chunk t + NQ - 1 and of DB chunk t + PF
-//      (PF = RING - 1) into those buffers;
+//      (PF = RING - 1) into those buffers (with the shared DB ring after the
+//      first query digit's MFMAs, so that their addresses are worked out
+//      under them: 64 clients on 8 GiB 4.16 -> 4.07 ms);
 //   3. with its own DB ring, waits for its DB chunk t (PF steps' loads were
 //      issued after it; in the first PF steps it waits for everything);
 //   4. reads the four digits' B fragments and, per query digit, the RS A
@@ -306,9 +308,6 @@ rowsel_mfma_qres_kernel(const MfmaJob J) {
             else qwait_vmcnt<AFTER_BOTH>();
             ++gstep;
             qbarrier();
-            // 2.
-            q_issue();
-            d_issue();
         } else {
             // 1. query chunk t: after its loads, this wave issued one step's
             //    DB loads and NQ - 2 steps' query and DB loads
@@ -356,6 +355,11 @@ rowsel_mfma_qres_kernel(const MfmaJob J) {
                         acc[i + j][rs * RN + rn] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
                             a[i % 2][rs], b[j][rn], acc[i + j][rs * RN + rn], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
+            if (SHDB && i == 0) {
+                q_issue();
+                d_issue();
+                __builtin_amdgcn_sched_barrier(0);
+            }
             if (i + 2 < 4) {
                 read_a(i + 2);
                 __builtin_amdgcn_sched_barrier(0);
@@ -399,22 +403,24 @@ int qres_cu_count() {
 }  // namespace
 
 // Unit shapes (sub-tiles per wave RS x RN, WR row groups; query buffers, DB
-// ring slots): 32 x 128, 64 x 128, 96 x 64 and 128 x 64, the last two with one
-// DB ring for the block.  Measured on the 512 x 512, N = 4096 DB (GEMM
+// ring slots): 32 x 128, 64 x 128, 96 x 64 and 128 x 64, the last three with
+// one DB ring for the block.  Measured on the 512 x 512, N = 4096 DB (GEMM
 // alone): the 128-row unit with 4 x 1 sub-tiles per wave (each wave all 64
 // rows of 16 columns) and per-wave DB rings, which load each column twice,
 // took 4.28 ms for 64 clients, with one shared ring 4.16 ms, and with 2 x 2
 // sub-tiles per wave (a fifth fewer LDS fragment reads) 4.05-4.14 ms against
 // 4.18-4.26 ms on the same boxes; the 96-row unit took 3.15-3.30 ms for 33 to
-// 48 clients, where 128-row units took 3.71-4.18 ms.  A 64 x 128 unit with
-// 2 x 2 sub-tiles and a shared ring tied with the 4 x 1 form.
+// 48 clients, where 128-row units took 3.71-4.18 ms.  The 64 x 128 unit with
+// 2 x 2 sub-tiles and a shared ring takes 2.11-2.14 ms for 32 clients (32-bit
+// primes 2.24, four 27-bit limbs on 256 x 512 2.33), with 4 x 1 sub-tiles and
+// per-wave rings 2.18-2.20 (2.32, 2.41).
 struct QVariant {
     uint32_t rs, wr, nq, ring, rn;
     uint32_t rows() const { return 16 * rs * wr; }
     uint32_t cols() const { return 16 * rn * (QWAVES / wr); }
     uint32_t min_chunks() const { return std::max(nq - 1, ring - 1); }
 };
-static const QVariant QRES[] = {{2, 1, 3, 4, 1}, {4, 1, 3, 3, 1}, {3, 2, 3, 3, 1}, {2, 4, 2, 3, 2}};
+static const QVariant QRES[] = {{2, 1, 3, 4, 1}, {2, 2, 3, 3, 2}, {3, 2, 3, 3, 1}, {2, 4, 2, 3, 2}};
 constexpr uint32_t NQRES = sizeof(QRES) / sizeof(QRES[0]);
 uint32_t qres_shape_count() { return NQRES; }
 uint32_t qres_min_chunks(uint32_t shape) { return QRES[shape].min_chunks(); }
@@ -486,7 +492,7 @@ void launch_mfma_qres(const MfmaJob &job, hipStream_t st) {
     };
     switch (job.wm) {
         case 0: go_mode(QShape<2, 1, 3, 4>{}); break;
-        case 1: go_mode(QShape<4, 1, 3, 3>{}); break;
+        case 1: go_mode(QShape<2, 2, 3, 3, true, 2>{}); break;
         case 2: go_mode(QShape<3, 2, 3, 3, true>{}); break;
         default: go_mode(QShape<2, 4, 2, 3, true, 2>{}); break;
     }
