@@ -20,8 +20,6 @@ void set_error(const std::string &msg) { g_last_error = msg; }
 void clear_error() { g_last_error.clear(); }
 
 // ------------------------------------------------------------------ memory
-static void trim_scratch();
-
 void *dev_alloc(size_t bytes) {
     void *p = nullptr;
     hipError_t e = hipMalloc(&p, bytes ? bytes : 1);
@@ -60,9 +58,10 @@ DevBuf::~DevBuf() { dev_free(ptr); }
 // not moved between stream handles: two streams never wait for each other's
 // scratch.  At most SCRATCH_KEEP bytes per device wait for a user (enough for
 // 64 clients on an 8 GiB DB, query transform included); the longest unused
-// ones go first, and all of them when a DB is freed or an allocation of the
-// library fails.  The memory itself comes from hipMallocAsync, as in captured
-// calls, whose allocations become nodes of the graph.
+// ones go first, and all of them when a DB is freed, when a server measures the
+// free memory and when an allocation of the library fails.  The memory itself
+// comes from hipMallocAsync, as in captured calls, whose allocations become
+// nodes of the graph.
 constexpr uint64_t SCRATCH_KEEP = 8ull << 30;
 
 struct ScratchBlock {
@@ -87,8 +86,7 @@ static void release_block(const ScratchBlock &b, hipStream_t st) {
     (void)hipEventDestroy(b.done);
 }
 
-// Gives back the current device's free blocks.
-static void trim_scratch() {
+void trim_scratch() {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return;
     std::lock_guard<std::mutex> lk(g_scratch_mu);
@@ -103,6 +101,9 @@ static void trim_scratch() {
         (void)hipEventDestroy(b.done);
     }
     g_scratch.swap(kept);
+    hipMemPool_t pool = nullptr;   // what they came from gives it back to the device
+    if (hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess) (void)hipMemPoolTrimTo(pool, 0);
+    (void)hipGetLastError();
 }
 
 // Whether st is being captured (or cannot say).

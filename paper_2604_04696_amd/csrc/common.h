@@ -204,6 +204,9 @@ struct StreamScratch {
     template <class T> T *as() const { return static_cast<T *>(ptr); }
 };
 
+// Gives back the current device's scratch blocks that no call uses.
+void trim_scratch();
+
 // Timing of each RowSel path's main kernel (pir_kernel_timing): while
 // enabled, a Scope records a pair of HIP events on the launch stream around
 // the launches made during its lifetime.

@@ -315,6 +315,7 @@ pir_status pir_server_create(const pir_db *db, const pir_server_opts *opts, pir_
             uint64_t budget = o.hbm_budget;
             if (!budget) {
                 size_t fr = 0, tot = 0;
+                trim_scratch();
                 PIR_HIP(hipMemGetInfo(&fr, &tot));
                 budget = (uint64_t)(fr * 0.9);
             }
