@@ -76,10 +76,18 @@ struct DigitCenter {
 };
 
 constexpr uint32_t DP_ROWS = 4;                         // rows per block
+constexpr uint32_t DP_REQUESTS = 32;                    // requests per launch of a table
 constexpr uint32_t DP_PTS = 128;                        // points per block
 constexpr uint32_t DP_PQ = DP_PTS / 4;                  // four-point groups per block
 constexpr uint32_t DP_THREADS = DP_PQ * 8 * DP_ROWS;    // a thread: four points x eight k of one row
 constexpr uint32_t DP_ROW = DP_PTS * 256 + 64;          // LDS bytes per row of the block (+ offset)
+
+// The requests of one launch (a server's admissions): their queries, and the
+// plane row of each one's first row.
+struct DigitRequests {
+    const uint32_t *src[DP_REQUESTS];
+    uint32_t row[DP_REQUESTS];
+};
 
 // LDS byte offset of the 16-byte piece kq (k = 16 kq .. 16 kq + 15) of
 // digit d of point pp in row rr.
@@ -87,12 +95,16 @@ __device__ __forceinline__ uint32_t dp_lds(uint32_t rr, uint32_t pp, uint32_t d,
     return rr * DP_ROW + pp * 256 + ((d ^ ((pp >> 4) & 3)) * 64) + ((kq ^ ((pp >> 2) & 3)) * 16);
 }
 
-template <bool CENTER, bool VEC>
+// TABLE: rows 2i and 2i + 1 are those of request i, at tab.src[i] and s_r
+// further, and go to plane rows tab.row[i] and + 1 (src and row0 unused).
+static_assert(DP_ROWS == 4, "a block's rows are those of two requests");
+
+template <bool CENTER, bool VEC, bool TABLE>
 __global__ void __launch_bounds__(DP_THREADS)
 digit_planes_kernel(const uint32_t *__restrict__ src, uint64_t s_r, uint64_t s_k,
                     int8_t *__restrict__ dst, uint32_t R, uint32_t r_valid, uint32_t P,
                     uint32_t kp, uint32_t klo, uint32_t khi, uint32_t kvalid, uint32_t kblk0,
-                    uint32_t nkblk, uint32_t RS, uint32_t row0, DigitCenter dc) {
+                    uint32_t nkblk, uint32_t RS, uint32_t row0, DigitCenter dc, DigitRequests tab) {
     __shared__ __attribute__((aligned(16))) uint8_t tile[DP_ROWS * DP_ROW];
     const uint32_t tid = threadIdx.x;
     uint64_t b = blockIdx.x;
@@ -112,7 +124,9 @@ digit_planes_kernel(const uint32_t *__restrict__ src, uint64_t s_r, uint64_t s_k
     for (int i = 0; i < 8; ++i) {
         const uint32_t k = k0 + kg * 8 + i;
         const bool in = r < r_valid && k >= klo && k < khi;
-        const uint32_t *at = src + (uint64_t)r * s_r + (uint64_t)(k - klo) * s_k + pb4;
+        const uint32_t *from = TABLE ? tab.src[rr < 2 ? r0 / 2 : min(r0 / 2 + 1, DP_REQUESTS - 1)] + (r % 2) * s_r
+                                     : src + (uint64_t)r * s_r;
+        const uint32_t *at = from + (uint64_t)(k - klo) * s_k + pb4;
         if (VEC) {   // P is a multiple of 4: the four points are all in or all out
             v[i] = in && pb4 < P ? ld_nt(reinterpret_cast<const uint4 *>(at)) : make_uint4(0, 0, 0, 0);
         } else {
@@ -168,7 +182,9 @@ digit_planes_kernel(const uint32_t *__restrict__ src, uint64_t s_r, uint64_t s_k
         const uint32_t hv = std::min(kc + 16, kvalid);   // k >= kvalid is padding
         const bool inside = kc >= klo && hv <= khi;
         const uint4 x = *reinterpret_cast<const uint4 *>(tile + dp_lds(orr, pp, d, kq));
-        int8_t *o = dst + ((((uint64_t)(p0 + pp) * 4 + d) * (kp / 64) + kc / 64) * RS + row0 + orow) * 64 + kc % 64;
+        const uint32_t prow = TABLE ? tab.row[orr < 2 ? r0 / 2 : min(r0 / 2 + 1, DP_REQUESTS - 1)] + orow % 2
+                                    : row0 + orow;
+        int8_t *o = dst + ((((uint64_t)(p0 + pp) * 4 + d) * (kp / 64) + kc / 64) * RS + prow) * 64 + kc % 64;
         if (inside) {
             st_nt(reinterpret_cast<uint4 *>(o), x);
         } else {
@@ -184,7 +200,7 @@ digit_planes_kernel(const uint32_t *__restrict__ src, uint64_t s_r, uint64_t s_k
 static void launch_digit_planes(const pir_db &db, const uint32_t *src, uint64_t s_r, uint64_t s_k, int8_t *dst,
                                 uint32_t R, uint32_t r_valid, uint32_t P, uint32_t kp,
                                 uint32_t klo, uint32_t khi, uint32_t kvalid, hipStream_t st,
-                                uint32_t RS = 0, uint32_t row0 = 0) {
+                                uint32_t RS = 0, uint32_t row0 = 0, const DigitRequests *tab = nullptr) {
     if (!RS) RS = R;
     if (klo >= khi || R == 0) return;
     // blocks cover [klo, khi); when khi = D0 the last block also zero-fills
@@ -197,10 +213,19 @@ static void launch_digit_planes(const pir_db &db, const uint32_t *src, uint64_t 
     for (uint32_t l = 0; l < db.p.nprimes; ++l) dc.q[l] = db.p.q[l];
     dc.n = db.p.n;
     // 16-byte loads need an aligned source and whole four-point groups
-    const bool vec = reinterpret_cast<uintptr_t>(src) % 16 == 0 && P % 4 == 0 && s_r % 4 == 0 && s_k % 4 == 0;
+    // (a table's are: the server takes no other query, and a polynomial has at least 8 points)
+    const bool vec = tab || (reinterpret_cast<uintptr_t>(src) % 16 == 0 && P % 4 == 0 && s_r % 4 == 0 && s_k % 4 == 0);
     auto go = [&](auto center, auto vec4) {
-        digit_planes_kernel<decltype(center)::value, decltype(vec4)::value><<<(uint32_t)blocks, DP_THREADS, 0, st>>>(
-            src, s_r, s_k, dst, R, r_valid, P, kp, klo, khi, kvalid, kb0, nkb, RS, row0, dc);
+        constexpr bool C = decltype(center)::value, V = decltype(vec4)::value;
+        auto kern = [&](auto table) {
+            digit_planes_kernel<C, V, decltype(table)::value><<<(uint32_t)blocks, DP_THREADS, 0, st>>>(
+                src, s_r, s_k, dst, R, r_valid, P, kp, klo, khi, kvalid, kb0, nkb, RS, row0, dc,
+                tab ? *tab : DigitRequests{});
+        };
+        if constexpr (V) {
+            if (tab) return kern(std::true_type{});
+        }
+        kern(std::false_type{});
     };
     if (db.wide) {
         if (vec) go(std::true_type{}, std::true_type{});
@@ -1081,6 +1106,22 @@ void launch_query_digits_rows(const pir_db &db, const uint32_t *q, uint32_t rows
     const uint32_t P = p.n * p.nprimes;
     launch_digit_planes(db, q, (uint64_t)p.d0 * P, P, qd, rows, rows, P, (p.d0 + 63) / 64 * 64, 0, p.d0, p.d0, st,
                         mstride, row0);
+}
+
+void launch_query_digits_requests(const pir_db &db, const uint32_t *const *q, const uint32_t *row, uint32_t count,
+                                  int8_t *qd, uint32_t mstride, hipStream_t st) {
+    const auto &p = db.p;
+    const uint32_t P = p.n * p.nprimes;
+    for (uint32_t i = 0; i < count; i += DP_REQUESTS) {
+        const uint32_t c = std::min(count - i, DP_REQUESTS);
+        DigitRequests tab{};
+        for (uint32_t j = 0; j < c; ++j) {
+            tab.src[j] = q[i + j];
+            tab.row[j] = row[i + j];
+        }
+        launch_digit_planes(db, nullptr, (uint64_t)p.d0 * P, P, qd, 2 * c, 2 * c, P, (p.d0 + 63) / 64 * 64, 0, p.d0,
+                            p.d0, st, mstride, 0, &tab);
+    }
 }
 
 void launch_rowsel_mfma(const pir_db &db, const uint32_t *q, uint32_t B, uint32_t *out,

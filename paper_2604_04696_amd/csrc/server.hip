@@ -190,7 +190,12 @@ struct pir_server {
         }
     }
 
+    // The queries admitted at a step boundary are ingested together: a launch for
+    // one request's two rows leaves half of each block's rows empty (48 requests
+    // of 32 MiB on 32 slots: 5.81 ms with one launch each, 5.74 together).
     void admit() {
+        std::vector<const uint32_t *> queries;
+        std::vector<uint32_t> rows;
         for (uint32_t s = 0; s < capacity && !waitq.empty(); ++s) {
             if (slots[s].state != FREE) continue;
             const Pending pr = waitq.front();
@@ -201,10 +206,12 @@ struct pir_server {
             sl.remaining = chunks;
             sl.t_submit = pr.t_submit;
             sl.t_admit = now_s();
-            launch_query_digits_rows(*db, pr.r.q_dev, 2, qd, mstride, 2 * s, st);
+            queries.push_back(pr.r.q_dev);
+            rows.push_back(2 * s);
             set_rows(s, pr.r.out_dev);
             ++admitted;
         }
+        launch_query_digits_requests(*db, queries.data(), rows.data(), (uint32_t)queries.size(), qd, mstride, st);
         flush_rows();
     }
 
