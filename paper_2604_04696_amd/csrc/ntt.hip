@@ -26,6 +26,7 @@
 // clients).  One pass cannot write whole plane rows: a row needs the same
 // point of all the 64 k of a chunk, i.e. 64 full polynomials (1 MiB at
 // N = 4096) in one block.
+#include <algorithm>
 #include <map>
 #include <mutex>
 #include <tuple>
@@ -441,54 +442,73 @@ bool launch_ntt_layout_valu(const pir_db &db, const uint32_t *src, uint32_t row0
 
 // ------------------------------------------------------------ DB layouts
 // NTT-domain source rows [nrows][D1][L*N/4] -> VALU layout [L*N/4][S][D0][W]
-// (16-byte vectors of four points, 256-column strips, see DbLayoutValu).
-// Tiles of 32 point groups x 64 columns of one row pass through LDS: 512-byte
-// read runs and 1 KiB write runs.  HBM-bound: 1 GiB in 0.36 ms (5.9 TB/s read
-// and written); one vector per thread straight from the source, whose lanes
-// read 16 bytes each from as many records, took 1.24 ms.
-constexpr uint32_t LV_G = 32, LV_C = 64;
-static_assert(VALU_STRIP % LV_C == 0, "a tile's columns lie in one strip");
+// (16-byte vectors of four points, 256-column strips, see DbLayoutValu).  The
+// records of a strip, row after row, are one run of nrows * W vectors for each
+// point group, so a tile takes LG groups of LC = 2048 / LG consecutive records,
+// whatever the strip's width, through LDS: with LG = 32 512-byte read runs and
+// 1 KiB write runs.  HBM-bound: 1 GiB in 0.36 ms (5.9 TB/s read and written);
+// one vector per thread straight from the source, whose lanes read 16 bytes each
+// from as many records, took 1.24 ms.  (Tiles of 64 columns of a single row are
+// mostly empty where D1 is small: 16384 x 1 records of 32 KiB 2.12 ms, these
+// 0.19.)  Non-temporal both ways: 128 MiB that no cache holds 49 us, with plain
+// loads and stores 74 (42 against 48 where the same 128 MiB are loaded over and
+// over).  The blocks walk the tiles: a launch holds fewer than 2^32 threads.
+constexpr uint32_t LV_TILE = 2048, LV_THREADS = 256, LV_BLOCKS = 1u << 20;
 
-__global__ void __launch_bounds__(256)
-db_layout_valu_kernel(const uint4 *__restrict__ src, uint4 *__restrict__ dst, uint32_t row0, uint32_t d0,
-                      uint32_t d1, uint32_t GG, uint32_t nblk_g, uint32_t nblk_n) {
-    __shared__ uint4 tile[LV_G][LV_C + 1];
+template <uint32_t LG>
+__global__ void __launch_bounds__(LV_THREADS)
+db_layout_valu_kernel(const uint4 *__restrict__ src, uint4 *__restrict__ dst, uint32_t row0, uint32_t nrows,
+                      uint32_t d0, uint32_t d1, uint32_t GG, uint32_t nblk_g, uint32_t per_strip, uint64_t tiles) {
+    constexpr uint32_t LC = LV_TILE / LG, STEP = LV_THREADS / LG;   // (records between a thread's loads)
+    static_assert(LC * LG == LV_TILE && STEP * LG == LV_THREADS, "a tile divides among the threads");
+    __shared__ uint4 tile[LG][LC + 1];
     const uint32_t tid = threadIdx.x;
-    uint32_t b = blockIdx.x;
-    const uint32_t g0 = b % nblk_g * LV_G;
-    b /= nblk_g;
-    const uint32_t n0 = b % nblk_n * LV_C, r = b / nblk_n;
-    uint4 v[LV_G * LV_C / 256];
+    for (uint64_t b = blockIdx.x; b < tiles; b += gridDim.x) {
+        const uint32_t g0 = (uint32_t)(b % nblk_g) * LG, eb = (uint32_t)(b / nblk_g), strip = eb / per_strip;
+        const uint32_t w = valu_strip_width(strip, d1), ne = nrows * w;   // records of the strip
+        const uint32_t e0 = (eb - strip * per_strip) * LC;
+        uint32_t e = e0 + tid / LG, r = e / w, c = e % w;
+        const uint32_t dr = STEP / w, dc = STEP % w;
+        uint4 v[LV_TILE / LV_THREADS];
 #pragma unroll
-    for (uint32_t j = 0; j < LV_G * LV_C / 256; ++j) {
-        const uint32_t gi = tid % LV_G, ci = j * (256 / LV_G) + tid / LV_G;
-        v[j] = g0 + gi < GG && n0 + ci < d1 ? ld_nt(src + ((uint64_t)r * d1 + n0 + ci) * GG + g0 + gi)
-                                            : make_uint4(0, 0, 0, 0);
-    }
+        for (uint32_t j = 0; j < LV_TILE / LV_THREADS; ++j) {
+            v[j] = g0 + tid % LG < GG && e < ne
+                       ? ld_nt(src + ((uint64_t)r * d1 + strip * VALU_STRIP + c) * GG + g0 + tid % LG)
+                       : make_uint4(0, 0, 0, 0);
+            e += STEP, r += dr, c += dc;
+            if (c >= w) c -= w, ++r;
+        }
 #pragma unroll
-    for (uint32_t j = 0; j < LV_G * LV_C / 256; ++j) tile[tid % LV_G][j * (256 / LV_G) + tid / LV_G] = v[j];
-    __syncthreads();
-    const uint32_t strip = n0 / VALU_STRIP, w = valu_strip_width(strip, d1);
+        for (uint32_t j = 0; j < LV_TILE / LV_THREADS; ++j) tile[tid % LG][j * STEP + tid / LG] = v[j];
+        __syncthreads();
 #pragma unroll
-    for (uint32_t j = 0; j < LV_G * LV_C / 256; ++j) {
-        const uint32_t ci = tid % LV_C, gi = j * (256 / LV_C) + tid / LV_C;
-        if (g0 + gi < GG && n0 + ci < d1)
-            st_nt(dst + valu_strip_base(g0 + gi, strip, d0, d1) + (uint64_t)(row0 + r) * w + (n0 + ci) % VALU_STRIP,
-                  tile[gi][ci]);
+        for (uint32_t j = 0; j < LV_TILE / LV_THREADS; ++j) {
+            const uint32_t f = j * LV_THREADS + tid, ci = f % LC, gi = f / LC;
+            if (g0 + gi < GG && e0 + ci < ne)
+                st_nt(dst + valu_strip_base(g0 + gi, strip, d0, d1) + (uint64_t)row0 * w + e0 + ci, tile[gi][ci]);
+        }
+        __syncthreads();
     }
 }
 
 void launch_db_layout_valu(const pir_db &db, const uint32_t *ntt_src, uint32_t row0,
                            uint32_t nrows, hipStream_t st) {
     const auto &p = db.p;
+    if (!nrows) return;
     const uint32_t GG = p.nprimes * (p.n / 4);
-    const uint32_t nblk_g = (GG + LV_G - 1) / LV_G, nblk_n = (p.d1 + LV_C - 1) / LV_C;
-    const uint64_t blocks = (uint64_t)nrows * nblk_g * nblk_n;
-    if (!blocks) return;
-    if (blocks >= (1ull << 31)) PIR_FAIL(PIR_EINVAL, "layout launch too large");
-    db_layout_valu_kernel<<<(uint32_t)blocks, 256, 0, st>>>(reinterpret_cast<const uint4 *>(ntt_src),
-                                                            reinterpret_cast<uint4 *>(db.valu.data), row0, p.d0,
-                                                            p.d1, GG, nblk_g, nblk_n);
+    auto go = [&](auto lg) {
+        constexpr uint32_t LG = decltype(lg)::value, LC = LV_TILE / LG;
+        const uint32_t nblk_g = (GG + LG - 1) / LG, full = p.d1 / VALU_STRIP, rest = p.d1 % VALU_STRIP;
+        const uint32_t per_strip = (nrows * VALU_STRIP + LC - 1) / LC;   // (nrows <= 65536)
+        const uint64_t tiles = (uint64_t)nblk_g * ((uint64_t)full * per_strip + (nrows * rest + LC - 1) / LC);
+        db_layout_valu_kernel<LG><<<(uint32_t)std::min<uint64_t>(tiles, LV_BLOCKS), LV_THREADS, 0, st>>>(
+            reinterpret_cast<const uint4 *>(ntt_src), reinterpret_cast<uint4 *>(db.valu.data), row0, nrows, p.d0, p.d1,
+            GG, nblk_g, per_strip, tiles);
+    };
+    // rings with fewer groups take tiles with fewer, and more records
+    if (GG >= 32) go(std::integral_constant<uint32_t, 32>{});
+    else if (GG >= 8) go(std::integral_constant<uint32_t, 8>{});
+    else go(std::integral_constant<uint32_t, 2>{});
     PIR_LAUNCH_CHECK();
 }
 
