@@ -517,9 +517,15 @@ pir_status pir_db_load_ntt(pir_db *db, const uint32_t *src, uint32_t row0, uint3
             return;
         }
         // coefficient domain, a VALU layout and whole 64-row chunks of the
-        // digit planes: the transform writes the one, the other is made from it
+        // digit planes: the transform writes the one, the other is made from it,
+        // 64 columns a block.  With few columns those blocks are mostly empty and
+        // the planes from an NTT-domain copy cost less (us, copy and no copy, 30-bit
+        // primes: 1024 rows, N = 4096, 1 column 57 and 210, 8 columns 320 and 297;
+        // 4096 rows, N = 1024, 8 columns 293 and 271, 12 columns 452 and 434, N = 4096,
+        // 8 columns 1190 and 1408; 32-bit primes, 1024 rows, N = 4096, 8 columns 386 and
+        // 470, 12 columns 563 and 613, 16 columns 751 and 728).
         const bool mfma = db->layouts & PIR_LAYOUT_MFMA, valu = db->layouts & PIR_LAYOUT_VALU;
-        const bool whole = row0 % 64 == 0 && ((row0 + nrows) % 64 == 0 || row0 + nrows == p.d0) &&
+        const bool whole = p.d1 >= 12 && row0 % 64 == 0 && ((row0 + nrows) % 64 == 0 || row0 + nrows == p.d0) &&
                            p.nprimes * (p.n / 4ull) * ((p.d1 + 63) / 64) * (nrows / 64 + 1) < (1ull << 31);
         if (valu && (!mfma || whole) && launch_ntt_layout_valu(*db, src, row0, nrows, st)) {
             if (mfma) launch_db_planes_from_valu(*db, row0, nrows, st);
