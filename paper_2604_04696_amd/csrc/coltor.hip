@@ -408,14 +408,15 @@ rgsw_permute_kernel(const uint32_t *__restrict__ in, uint32_t *__restrict__ out,
     }
 }
 
-// SPLIT: where the nodes leave CUs idle (fewer than 256 (node, limb) blocks: a
-// tournament of one client has 64 nodes and fewer in seven of nine stages, one
-// block of ten transforms takes 26 us, ten of one transform 7 us and their sum
-// 6-7 us; with 32 nodes, four parts, 20 and 6 us), a (node, limb) is split into `parts`
-// blocks of digit polynomials; `rgsw_p` then holds the rows as given (gathered:
-// a few digits a block cost less than the permuting launch), and the block's
-// sums go to `out` as [part][node][limb][2][N] residues in the transform's
-// order, for coltor_sum_kernel to add up.
+// SPLIT: where the nodes leave CUs idle (up to 256 (node, limb) blocks, up to 128
+// from N = 8192 on, see split_blocks: a tournament of one client has 64 nodes and
+// fewer in seven of nine stages, one block of ten transforms takes 26 us, ten of
+// one transform 7 us and their sum 6-7 us; with 32 nodes, four parts, 20 and
+// 6 us), a (node, limb) is split into `parts` blocks of digit polynomials;
+// `rgsw_p` then holds the rows as given (gathered: a few digits a block cost less
+// than the permuting launch), and the block's sums go to `out` as
+// [part][node][limb][2][N] residues in the transform's order, for
+// coltor_sum_kernel to add up.
 template <int LOGN, int MODE, bool SPLIT>
 __global__ void __launch_bounds__((1u << LOGN) / QR)
 coltor_mac_reg_kernel(const uint32_t *__restrict__ ct, const uint32_t *__restrict__ rgsw_p,
@@ -633,8 +634,11 @@ void coltor_check_gadget(const pir_params &ring, uint32_t log2z, uint32_t ell) {
                  ring.n * ring.nprimes);
 }
 
-// Blocks that keep the CUs busy (two each).
-constexpr uint64_t SPLIT_BLOCKS = 512;
+// Blocks of the products that the CUs hold, up to which nodes are split: two a CU,
+// from N = 8192 on (512 threads of more than 128 registers) one.  256 nodes of
+// one limb, in one part and in two: N = 8192, ell = 4 96 and 139 us, N = 16384,
+// ell = 2 202 and 269; two 30-bit limbs of N = 4096, ell = 3, 128 nodes 58 and 52.
+static uint64_t split_blocks(uint32_t n) { return n > 4096 ? 256 : 512; }
 
 void launch_coltor_stage(const pir_params &ring, const uint32_t *ct, uint32_t B, uint32_t ncols,
                          const uint32_t *rgsw, uint32_t log2z, uint32_t ell, uint32_t *out, hipStream_t st) {
@@ -699,7 +703,7 @@ void launch_coltor_stage(const pir_params &ring, const uint32_t *ct, uint32_t B,
         const uint32_t T = n / QR;
         uint32_t G = 1;
         for (uint32_t d = 2; d <= L; ++d)
-            if (L % d == 0 && d * T <= (nodes * 2 <= SPLIT_BLOCKS / 2 ? 1024 : 512)) G = d;
+            if (L % d == 0 && d * T <= (nodes * 2 <= 256 ? 1024 : 512)) G = d;
         auto go1 = [&](auto kern) {
             PIR_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
@@ -732,7 +736,7 @@ void launch_coltor_stage(const pir_params &ring, const uint32_t *ct, uint32_t B,
         // with idle CUs: the digit polynomials of a (node, limb) in several
         // blocks, else the RGSW rows in the transform's register order, then
         // one block each
-        const uint32_t most = (uint32_t)(SPLIT_BLOCKS / (nodes * L)), per = most ? (2 * ell + most - 1) / most : 2 * ell;
+        const uint32_t most = (uint32_t)(split_blocks(n) / (nodes * L)), per = most ? (2 * ell + most - 1) / most : 2 * ell;
         const uint32_t parts = (2 * ell + per - 1) / per;
         const bool split = parts > 1;
         const uint64_t rg_words = (uint64_t)B * 4 * ell * L * n;
