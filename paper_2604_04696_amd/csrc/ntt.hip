@@ -295,10 +295,10 @@ void launch_ntt(const uint32_t *in, uint32_t *out, uint64_t records, uint32_t n,
         pr.qn[l] = t.qn;
         wide = wide || q[l] >= WIDE_Q;
     }
-    // gridDim.x is limited to 2^31 - 1: at most 2^28 records of four limbs a launch
-    constexpr uint64_t MOST = 1ull << 28;
-    for (uint64_t r0 = 0; r0 < records; r0 += MOST) {
-        const uint32_t nr = (uint32_t)std::min(records - r0, MOST);
+    // a launch holds fewer than 2^32 threads (N/16 a polynomial, for small rings 32)
+    const uint64_t most = (1ull << 31) / ((uint64_t)L * std::max(n / QR, 32u));
+    for (uint64_t r0 = 0; r0 < records; r0 += most) {
+        const uint32_t nr = (uint32_t)std::min(records - r0, most);
         const uint32_t *src = in + r0 * L * n;
         uint32_t *dst = out + r0 * L * n;
         auto go = [&](auto inv, auto w) {
