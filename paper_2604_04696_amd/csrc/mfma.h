@@ -71,9 +71,10 @@ MfmaJob make_qres_job(const pir_db &db, const int8_t *qd, uint32_t mstride, uint
                       uint32_t shape);
 void launch_mfma_qres(const MfmaJob &job, hipStream_t st);
 // The small-batch kernel (rowsel_mfma_direct.hip): the rows its query planes
-// need for a job of `rows` query rows, 0 where another kernel takes the job.
+// need for a job of `rows` query rows, d1 columns, nkc 64-row chunks of k and
+// `groups` point groups, 0 where another kernel takes the job.
 // The job's mp is the row stride of its staging (rows past it are dropped).
-uint32_t direct_rows(uint32_t rows);
+uint32_t direct_rows(uint32_t rows, uint32_t d1, uint32_t nkc, uint32_t groups);
 void launch_mfma_direct(const MfmaJob &job, hipStream_t st);
 // Staging row stride of a DB with d1 columns (16-byte aligned rows).
 inline uint32_t staging_stride(uint32_t d1) { return (d1 + 3) / 4 * 4; }

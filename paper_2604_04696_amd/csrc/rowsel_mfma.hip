@@ -1129,7 +1129,7 @@ void launch_rowsel_mfma(const pir_db &db, const uint32_t *q, uint32_t B, uint32_
     // scratch: query digit planes [P][4][Kp/64][Mp][64], then the output
     // staging [P][rows][sstride]
     const uint32_t mp = (2 * B + 31) / 32 * 32;
-    const uint32_t drows = direct_rows(2 * B);
+    const uint32_t drows = direct_rows(2 * B, db.p.d1, db.mfma.kp / 64, (uint32_t)(db.slots() / 4));
     const bool qres = !drows && qres_preferred(mp, db.mfma.kp / 64);
     const uint32_t shape = qres_shape_for(mp), bm = qres_rows(shape);
     const uint32_t mstride = drows ? drows : qres ? (mp + bm - 1) / bm * bm : mp;

@@ -315,11 +315,21 @@ static bool direct_narrow(uint32_t d1) { return (d1 + 255) / 256 * 256 > d1 + d1
 // N = 4096 DB: 8 clients 1.54 ms against 1.77, 4 clients with 32-bit primes
 // 1.47 against 1.79, 16 clients 1.73 against 1.79, and on ragged or small DBs
 // the same or faster (1300 x 37, 15 clients 0.19 against 0.20 ms); at 64 rows
-// the query-resident kernel is the faster one, 2.12 against 2.36.
-uint32_t direct_rows(uint32_t rows) {
+// the query-resident kernel is the faster one, 2.12 against 2.36.  With fewer than
+// 64 columns half of a block's waves and more have none, and with more than one
+// LDS segment of k the block waits for each: there 32 rows are the tiled
+// kernel's, which takes four points a tile, where these give every CU one (16
+// clients, N = 1024, us: 4096 x 16 479 and 459, 4096 x 48 538 and 493, 4096 x 64 567
+// and 568, 4096 x 80 626 and 683, 640 x 32 96 and 85; in one segment 256 x 4 42 and 47;
+// 4096 x 16 at N = 256, 128 tiles, 132 and 228).  16 rows are not (4 clients,
+// 4096 x 48 at N = 1024 350 and 488).
+constexpr uint32_t DSEG = 8;   // chunks of k per LDS segment, every shape
+
+uint32_t direct_rows(uint32_t rows, uint32_t d1, uint32_t nkc, uint32_t groups) {
     if (const char *e = std::getenv("PIR_MFMA_KERNEL"))   // a kernel forced by name (tuning runs, tests)
         if (!std::strcmp(e, "qres") || !std::strcmp(e, "tile")) return 0;
-    return rows <= 16 ? 16 : rows <= 32 ? 32 : 0;
+    if (rows <= 16) return 16;
+    return rows > 32 || (d1 < 64 && nkc > DSEG && groups >= (uint32_t)direct_cu_count()) ? 0 : 32;
 }
 
 void launch_mfma_direct(const MfmaJob &job0, hipStream_t st) {
@@ -353,9 +363,9 @@ void launch_mfma_direct(const MfmaJob &job0, hipStream_t st) {
             default: go(shape, std::integral_constant<int, RECOMB_WIDE>{}); break;
         }
     };
-    if (job.mp > 16) go_mode(DShape<2, 1, 8, 3, 8>{});
-    else if (direct_narrow(job.d1)) go_mode(DShape<1, 1, 8, 3, 8>{});
-    else go_mode(DShape<1, 2, 8, 2, 8>{});
+    if (job.mp > 16) go_mode(DShape<2, 1, 8, 3, DSEG>{});
+    else if (direct_narrow(job.d1)) go_mode(DShape<1, 1, 8, 3, DSEG>{});
+    else go_mode(DShape<1, 2, 8, 2, DSEG>{});
     PIR_LAUNCH_CHECK();
 }
 

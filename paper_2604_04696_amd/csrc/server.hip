@@ -235,7 +235,7 @@ struct pir_server {
         const uint32_t mp = (rows + 31) / 32 * 32;
         MfmaJob job;
         // (or, up to 16 clients, the small-batch kernel)
-        if (direct_rows(rows) && !shape_forced()) {
+        if (direct_rows(rows, db->p.d1, db->mfma.kp / 64, ng) && !shape_forced()) {
             job = make_mfma_job(*db, qd, stage, hi + 1, 0, 2);
             job.mp = rows;
             job.mstride = mstride;
