@@ -31,6 +31,17 @@
  * A pir_db may be read by concurrent calls; loading into it must not overlap
  * a RowSel call that reads it.
  *
+ * Scratch: a call's temporary device memory ("stream-ordered scratch" below) is
+ * in use until the stream passes the call and is then kept for later calls.  The
+ * library holds up to 8 GiB of it per device, or the bytes that PIR_SCRATCH_KEEP
+ * in the environment names (0: none), and when it takes more, no more than stays
+ * free on the device beside it; calls beyond that take their scratch from the
+ * runtime and return it.  Memory that is held is not there for other allocators
+ * of the process: what no call uses goes back to the device with
+ * pir_scratch_trim, when a DB is freed, when a server measures the free memory
+ * and when an allocation of the library itself runs out of memory.  Under
+ * stream capture the allocations are nodes of the graph.
+ *
  * Errors: every call returns pir_status; no C++ exception crosses the ABI.
  * Argument and shape checks fail with PIR_EINVAL before anything is
  * enqueued; pir_last_error() returns a thread-local message describing the
@@ -111,8 +122,11 @@ pir_status pir_db_create(const pir_params *params, uint32_t layouts, pir_db **ou
  * natural point order ahat_i = a(psi_l^(2i+1)), psi_l = g^((q_l-1)/2N),
  * g the smallest generator mod q_l (sec. 2.4.1).  PIR_DOMAIN_NTT: values
  * must be residues < q_l and are taken as they are.  The source is only
- * read; it may be freed once the stream passes the call.  Temporary device
- * memory of nrows*D1*L*N*4 bytes is used for COEFF input. */
+ * read; it may be freed once the stream passes the call.  COEFF input whose
+ * transform cannot write the VALU layout directly (no VALU layout, N outside
+ * 256..4096, or both layouts with fewer than 12 columns or a row range that cuts
+ * a 64-row chunk) takes stream-ordered scratch of nrows*D1*L*N*4 bytes, at most
+ * 1 GiB or one row. */
 pir_status pir_db_load_ntt(pir_db *db, const uint32_t *src_dev, uint32_t row0,
                            uint32_t nrows, pir_domain domain, void *hip_stream);
 
@@ -210,7 +224,9 @@ pir_status pir_rowsel_coeff(const pir_db *db, const uint32_t *q_coeff_dev, uint3
  * prime, else PIR_EINVAL.  B = 0 is a no-op; ncols >= 1 otherwise.
  * Stream-ordered scratch holds the digits (B * ceil(ncols/2) * 2 * ell * N
  * int32) and, for N >= 256, the RGSW rows permuted to the transforms'
- * register order (the size of rgsw_dev).  Asynchronous on hip_stream like
+ * register order (the size of rgsw_dev), or with B * ceil(ncols/2) * L up to 256
+ * (128 from N = 8192 on) partial sums in their place (at most 1024 * N words).
+ * Asynchronous on hip_stream like
  * pir_rowsel; a tournament is one call per stage on the previous output. */
 pir_status pir_coltor_stage(const pir_params *ring, const uint32_t *ct_dev, uint32_t B, uint32_t ncols,
                             const uint32_t *rgsw_dev, uint32_t log2z, uint32_t ell, uint32_t *out_dev,
@@ -365,6 +381,12 @@ pir_status pir_server_get_stats(const pir_server *srv, pir_server_stats *out);
 void pir_server_destroy(pir_server *srv);
 
 /* ---------------------------------------------------------------- helpers */
+/* Gives the scratch that the library holds on the current device and no call
+ * uses (see above) back to the device, so that other allocators can have it, and
+ * stores its bytes in *freed if freed is not NULL.  Waits for the device.  Not
+ * under stream capture. */
+pir_status pir_scratch_trim(uint64_t *freed);
+
 /* Negacyclic NTT / inverse NTT of `count` contiguous length-n polynomials
  * mod prime q < 2^32, q = 1 (mod 2n) (same convention as pir_db_load_ntt).  Not part of RowSel's
  * hot path: used to build inputs and to check results (client-side

@@ -66,6 +66,7 @@ SIGNATURES = {
     "pir_serve_step": (_i32, [_vp, _vp, _u32, _vp, _u32, ctypes.POINTER(_u32)]),
     "pir_server_get_stats": (_i32, [_vp, _vp]),
     "pir_server_destroy": (None, [_vp]),
+    "pir_scratch_trim": (_i32, [ctypes.POINTER(_u64)]),
     "pir_ntt_forward": (_i32, [_vp, _vp, _u32, _u32, _u32, _vp]),
     "pir_ntt_inverse": (_i32, [_vp, _vp, _u32, _u32, _u32, _vp]),
     "pir_kernel_timing": (_i32, [_i32]),
@@ -384,6 +385,14 @@ def pir_server_destroy(srv: Server):
     if h:
         lib().pir_server_destroy(h)
     srv.live.clear()
+
+
+def pir_scratch_trim() -> int:
+    """Give the scratch that the library holds on the current device and no call
+    uses back to the device; returns its bytes."""
+    freed = _u64()
+    _check(lib().pir_scratch_trim(ctypes.byref(freed)), "pir_scratch_trim")
+    return freed.value
 
 
 def pir_ntt_forward(src, out, n: int, q: int, stream=None):

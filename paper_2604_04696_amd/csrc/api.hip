@@ -3,6 +3,7 @@
 #include <atomic>
 #include <cstdlib>
 #include <cstring>
+#include <map>
 #include <mutex>
 #include <string>
 #include <utility>
@@ -23,7 +24,7 @@ void clear_error() { g_last_error.clear(); }
 void *dev_alloc(size_t bytes) {
     void *p = nullptr;
     hipError_t e = hipMalloc(&p, bytes ? bytes : 1);
-    if (e != hipSuccess) {   // once more without the kept scratch blocks
+    if (e == hipErrorOutOfMemory) {   // once more without the kept scratch blocks
         (void)hipGetLastError();
         trim_scratch();
         e = hipMalloc(&p, bytes ? bytes : 1);
@@ -54,14 +55,22 @@ DevBuf::~DevBuf() { dev_free(ptr); }
 // A block goes back with an event recorded behind its last use, and whoever
 // takes it up waits for that event on its own stream (no wait at all where the
 // two are the same stream): a recycled stream handle or the per-thread default
-// stream, one handle for many streams, is ordered like any other.  Blocks are
-// not moved between stream handles: two streams never wait for each other's
-// scratch.  At most SCRATCH_KEEP bytes per device wait for a user (enough for
-// 64 clients on an 8 GiB DB, query transform included); the longest unused
-// ones go first, and all of them when a DB is freed, when a server measures the
-// free memory and when an allocation of the library fails.  The memory itself
-// comes from hipMallocAsync, as in captured calls, whose allocations become
-// nodes of the graph.
+// stream, one handle for many streams, is ordered like any other.  A call
+// takes a block of its own stream handle, else one whose event has passed, so
+// two streams never wait for each other's scratch and blocks of streams that
+// are gone serve others.
+//
+// The blocks of a device, in use or not, hold at most SCRATCH_KEEP bytes (enough
+// for 64 clients on an 8 GiB DB, query transform included), or what
+// PIR_SCRATCH_KEEP says, and no more than stays free beside them when one is
+// made; for a new one the longest unused ones go, if their events have passed.
+// A call that finds no room takes its scratch from the runtime's pool, as
+// captured calls do, whose allocations become nodes of the graph.  All unused
+// blocks go when pir_scratch_trim is called, a DB is freed, a server measures
+// the free memory or an allocation of the library runs out of memory.  They are
+// hipMalloc's: memory of the pool does not always leave it when it is freed
+// (allocated behind unfinished work, it stayed there after the free, a
+// synchronization of the device and a trim of the pool).
 constexpr uint64_t SCRATCH_KEEP = 8ull << 30;
 
 struct ScratchBlock {
@@ -73,37 +82,59 @@ struct ScratchBlock {
 };
 
 static std::mutex g_scratch_mu;
-static std::vector<ScratchBlock> g_scratch;   // free blocks, the longest unused first
+static std::vector<ScratchBlock> g_scratch;       // unused blocks, the longest unused first
+static std::map<int, uint64_t> g_scratch_held;    // bytes of a device's blocks, in use or not
 
-// Gives a free block's memory back, in order on st (any stream of its device).
-static void release_block(const ScratchBlock &b, hipStream_t st) {
-    if (hipStreamWaitEvent(st, b.done, 0) == hipSuccess) {
-        (void)hipFreeAsync(b.ptr, st);
-    } else {
-        (void)hipGetLastError();
-        (void)hipFree(b.ptr);   // waits for the device
-    }
+static uint64_t scratch_limit() {
+    const char *v = std::getenv("PIR_SCRATCH_KEEP");
+    return v && *v ? std::strtoull(v, nullptr, 0) : SCRATCH_KEEP;
+}
+
+// Allocations, frees, event queries and waits concern no captured work; in this
+// mode they do not break a capture that another thread has under way.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+static bool passed(const ScratchBlock &b) {
+    if (hipEventQuery(b.done) == hipSuccess) return true;
+    (void)hipGetLastError();   // (not ready is no error)
+    return false;
+}
+
+static void destroy_block(const ScratchBlock &b) {
+    (void)hipFree(b.ptr);   // (waits for the device)
     (void)hipEventDestroy(b.done);
 }
 
-void trim_scratch() {
+uint64_t trim_scratch() {
     int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return;
-    std::lock_guard<std::mutex> lk(g_scratch_mu);
-    std::vector<ScratchBlock> kept;
-    for (const ScratchBlock &b : g_scratch) {
-        if (b.device != dev) {
-            kept.push_back(b);
-            continue;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    std::vector<ScratchBlock> out;
+    uint64_t bytes = 0;
+    {
+        std::lock_guard<std::mutex> lk(g_scratch_mu);
+        out.reserve(g_scratch.size());
+        for (size_t i = 0; i < g_scratch.size();) {
+            if (g_scratch[i].device != dev) {
+                ++i;
+                continue;
+            }
+            bytes += g_scratch[i].bytes;
+            out.push_back(g_scratch[i]);
+            g_scratch.erase(g_scratch.begin() + i);
         }
-        (void)hipEventSynchronize(b.done);
-        (void)hipFree(b.ptr);
-        (void)hipEventDestroy(b.done);
+        g_scratch_held[dev] -= bytes;
     }
-    g_scratch.swap(kept);
-    hipMemPool_t pool = nullptr;   // what they came from gives it back to the device
+    RelaxedCapture relaxed;
+    for (const ScratchBlock &b : out) destroy_block(b);
+    hipMemPool_t pool = nullptr;   // and what calls without a block left there
+    (void)hipDeviceSynchronize();
     if (hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess) (void)hipMemPoolTrimTo(pool, 0);
     (void)hipGetLastError();
+    return bytes;
 }
 
 // Whether st is being captured (or cannot say).
@@ -114,44 +145,91 @@ static bool capturing(hipStream_t st) {
     return true;
 }
 
+// Takes up a block that fits: the smallest, unless it is far larger than asked
+// for, and one of this stream first.
+bool StreamScratch::take_block(size_t need) {
+    std::lock_guard<std::mutex> lk(g_scratch_mu);
+    size_t best = g_scratch.size();
+    auto look = [&](bool own) {
+        for (size_t i = 0; i < g_scratch.size(); ++i) {
+            const ScratchBlock &b = g_scratch[i];
+            if (b.device == device && (b.st == st) == own && b.bytes >= need && b.bytes / 4 <= need + (1u << 20) &&
+                (best == g_scratch.size() || b.bytes < g_scratch[best].bytes) && (own || passed(b)))
+                best = i;
+        }
+    };
+    look(true);
+    if (best == g_scratch.size()) look(false);
+    if (best == g_scratch.size()) return false;
+    if (hipStreamWaitEvent(st, g_scratch[best].done, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    ptr = g_scratch[best].ptr;
+    bytes = g_scratch[best].bytes;
+    done = g_scratch[best].done;
+    g_scratch.erase(g_scratch.begin() + best);
+    return true;
+}
+
+// A new block, if there is room for one.
+bool StreamScratch::make_block(size_t need) {
+    const uint64_t limit = scratch_limit();
+    if (need > limit) return false;
+    size_t fr = 0, all = 0;
+    if (hipMemGetInfo(&fr, &all) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    std::vector<ScratchBlock> out;
+    {
+        std::lock_guard<std::mutex> lk(g_scratch_mu);
+        uint64_t &held = g_scratch_held[device];
+        uint64_t after = held + need, left = fr > need ? fr - need : 0;
+        auto room = [&] { return after <= limit && after <= left; };
+        out.reserve(g_scratch.size());
+        for (size_t i = 0; !room() && i < g_scratch.size(); ++i) {
+            const ScratchBlock &b = g_scratch[i];
+            if (b.device != device || !passed(b)) continue;
+            out.push_back(b);
+            after -= b.bytes;
+            left += b.bytes;
+        }
+        if (!room()) return false;
+        for (const ScratchBlock &o : out)
+            g_scratch.erase(std::find_if(g_scratch.begin(), g_scratch.end(), [&](auto &b) { return b.ptr == o.ptr; }));
+        held = after;
+    }
+    for (const ScratchBlock &b : out) destroy_block(b);
+    hipError_t e = hipEventCreateWithFlags(&done, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipMalloc(&ptr, need);
+    if (e == hipSuccess) return true;
+    (void)hipGetLastError();
+    ptr = nullptr;
+    if (done) (void)hipEventDestroy(done);
+    done = nullptr;
+    std::lock_guard<std::mutex> lk(g_scratch_mu);
+    g_scratch_held[device] -= need;
+    return false;
+}
+
 StreamScratch::StreamScratch(size_t need, hipStream_t s) : st(s) {
     if (need == 0) return;
     bytes = need;
     PIR_HIP(hipGetDevice(&device));
-    keep = !capturing(st);
-    if (keep) {
-        // the smallest block that fits, unless it is far larger than asked for
-        std::lock_guard<std::mutex> lk(g_scratch_mu);
-        size_t best = g_scratch.size();
-        for (size_t i = 0; i < g_scratch.size(); ++i) {
-            const ScratchBlock &b = g_scratch[i];
-            if (b.device == device && b.st == st && b.bytes >= need && b.bytes / 4 <= need + (1u << 20) &&
-                (best == g_scratch.size() || b.bytes < g_scratch[best].bytes))
-                best = i;
-        }
-        if (best < g_scratch.size() && hipStreamWaitEvent(st, g_scratch[best].done, 0) == hipSuccess) {
-            ptr = g_scratch[best].ptr;
-            bytes = g_scratch[best].bytes;
-            done = g_scratch[best].done;
-            g_scratch.erase(g_scratch.begin() + best);
-            return;
-        }
-        (void)hipGetLastError();
-        if (hipEventCreateWithFlags(&done, hipEventDisableTiming) != hipSuccess) {
-            (void)hipGetLastError();
-            done = nullptr;
-            keep = false;
-        }
+    const bool captured = capturing(st);
+    if (!captured) {
+        RelaxedCapture relaxed;
+        if (take_block(need) || make_block(need)) return;
     }
     hipError_t e = hipMallocAsync(&ptr, bytes, st);
-    if (e != hipSuccess && keep) {   // once more without the kept blocks
+    if (e == hipErrorOutOfMemory && !captured) {   // once more without the unused blocks
         (void)hipGetLastError();
         trim_scratch();
         e = hipMallocAsync(&ptr, bytes, st);
     }
     if (e != hipSuccess) {
         ptr = nullptr;
-        if (done) (void)hipEventDestroy(done);
         (void)hipGetLastError();
         PIR_FAIL(e == hipErrorOutOfMemory ? PIR_ENOMEM : PIR_EDEVICE, "hipMallocAsync(%zu bytes) failed: %s",
                  bytes, hipGetErrorString(e));
@@ -160,29 +238,22 @@ StreamScratch::StreamScratch(size_t need, hipStream_t s) : st(s) {
 
 StreamScratch::~StreamScratch() {
     if (!ptr) return;
-    if (!keep || bytes > SCRATCH_KEEP || hipEventRecord(done, st) != hipSuccess) {
-        if (done) (void)hipEventDestroy(done);
+    if (!done) {
         (void)hipFreeAsync(ptr, st);
         return;
     }
+    RelaxedCapture relaxed;
+    const ScratchBlock b{ptr, bytes, st, done, device};
+    bool kept = hipEventRecord(done, st) == hipSuccess;
+    if (!kept) (void)hipGetLastError();
     try {
         std::lock_guard<std::mutex> lk(g_scratch_mu);
-        uint64_t total = bytes;
-        for (const ScratchBlock &b : g_scratch) total += b.device == device ? b.bytes : 0;
-        for (size_t i = 0; total > SCRATCH_KEEP && i < g_scratch.size();) {
-            if (g_scratch[i].device != device) {
-                ++i;
-                continue;
-            }
-            total -= g_scratch[i].bytes;
-            release_block(g_scratch[i], st);
-            g_scratch.erase(g_scratch.begin() + i);
-        }
-        g_scratch.push_back({ptr, bytes, st, done, device});
-    } catch (...) {
-        (void)hipFreeAsync(ptr, st);
-        (void)hipEventDestroy(done);
+        if (kept) g_scratch.push_back(b);
+        else g_scratch_held[device] -= bytes;
+    } catch (...) {   // no host memory for the list
+        kept = false;
     }
+    if (!kept) destroy_block(b);
 }
 
 // ------------------------------------------------------------- kernel timer
@@ -544,6 +615,13 @@ pir_status pir_db_load_ntt(pir_db *db, const uint32_t *src, uint32_t row0, uint3
             if (db->layouts & PIR_LAYOUT_VALU) launch_db_layout_valu(*db, tmp, row0 + r, nr, st);
             if (db->layouts & PIR_LAYOUT_MFMA) launch_db_layout_mfma(*db, tmp, row0 + r, nr, st);
         }
+    });
+}
+
+pir_status pir_scratch_trim(uint64_t *freed) {
+    return guarded([&] {
+        const uint64_t bytes = trim_scratch();
+        if (freed) *freed = bytes;
     });
 }
 

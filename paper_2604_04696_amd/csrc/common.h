@@ -186,26 +186,28 @@ struct DeviceGuard {
 void *dev_alloc(size_t bytes);   // throws PIR_ENOMEM
 void dev_free(void *p);
 
-// Stream-ordered temporary: a block that an earlier call on `st` left behind, or
-// a new one, at construction; handed back in stream order when the scope ends
-// (also when a later step of the call throws).  Allocation failure throws
-// PIR_ENOMEM.
+// Stream-ordered temporary: a block that an earlier call left behind, or a new
+// one, at construction; handed back in stream order when the scope ends (also
+// when a later step of the call throws).  Allocation failure throws PIR_ENOMEM.
 struct StreamScratch {
     void *ptr = nullptr;
     hipStream_t st = nullptr;
     size_t bytes = 0;             // of the block (at least what was asked for)
-    hipEvent_t done = nullptr;    // recorded when it is handed back
+    hipEvent_t done = nullptr;    // a kept block's: recorded when it is handed back
     int device = 0;
-    bool keep = false;            // handed back to the library, not to the runtime
     StreamScratch(size_t need, hipStream_t s);
     ~StreamScratch();
     StreamScratch(const StreamScratch &) = delete;
     StreamScratch &operator=(const StreamScratch &) = delete;
     template <class T> T *as() const { return static_cast<T *>(ptr); }
+
+private:
+    bool take_block(size_t need);
+    bool make_block(size_t need);
 };
 
-// Gives back the current device's scratch blocks that no call uses.
-void trim_scratch();
+// Gives back the current device's scratch blocks that no call uses; their bytes.
+uint64_t trim_scratch();
 
 // Timing of each RowSel path's main kernel (pir_kernel_timing): while
 // enabled, a Scope records a pair of HIP events on the launch stream around
