@@ -192,26 +192,31 @@ struct pir_server {
 
     // The queries admitted at a step boundary are ingested together: a launch for
     // one request's two rows leaves half of each block's rows empty (48 requests
-    // of 32 MiB on 32 slots: 5.81 ms with one launch each, 5.74 together).
+    // of 32 MiB on 32 slots: 5.81 ms with one launch each, 5.74 together).  A
+    // request leaves the queue once its query is on its way: where a launch
+    // fails, it waits on and is ingested again.
     void admit() {
+        std::vector<uint32_t> free_slots, rows;
         std::vector<const uint32_t *> queries;
-        std::vector<uint32_t> rows;
-        for (uint32_t s = 0; s < capacity && !waitq.empty(); ++s) {
+        for (uint32_t s = 0; s < capacity && free_slots.size() < waitq.size(); ++s) {
             if (slots[s].state != FREE) continue;
-            const Pending pr = waitq.front();
-            waitq.pop_front();
+            queries.push_back(waitq[free_slots.size()].r.q_dev);
+            rows.push_back(2 * s);
+            free_slots.push_back(s);
+        }
+        launch_query_digits_requests(*db, queries.data(), rows.data(), (uint32_t)queries.size(), qd, mstride, st);
+        for (const uint32_t s : free_slots) {
+            const Pending &pr = waitq.front();
+            set_rows(s, pr.r.out_dev);
             Slot &sl = slots[s];
             sl.state = ACTIVE;
             sl.id = pr.r.id;
             sl.remaining = chunks;
             sl.t_submit = pr.t_submit;
             sl.t_admit = now_s();
-            queries.push_back(pr.r.q_dev);
-            rows.push_back(2 * s);
-            set_rows(s, pr.r.out_dev);
+            waitq.pop_front();
             ++admitted;
         }
-        launch_query_digits_requests(*db, queries.data(), rows.data(), (uint32_t)queries.size(), qd, mstride, st);
         flush_rows();
     }
 
