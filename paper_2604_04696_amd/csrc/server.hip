@@ -12,6 +12,7 @@
 // results do not depend on the mix.  Slots pass FREE -> ACTIVE -> DRAINING
 // (last step launched; its output pointers are cleared on the stream right
 // away, so later steps cannot write to it) -> FREE (last step retired).
+#include <algorithm>
 #include <chrono>
 #include <deque>
 #include <unordered_set>
@@ -122,7 +123,10 @@ struct pir_server {
     int8_t *qd = nullptr;
     uint32_t *stage = nullptr;
     uint64_t *row_dst_dev = nullptr;    // per row: destination of its results (0 = discard)
-    RowUpdates pending_rows{};          // table updates not yet launched
+    // destinations per row as the table is to have them, and the rows whose entry is not launched yet
+    std::vector<uint64_t> row_dst;
+    std::vector<uint32_t> dirty_rows;   // (each once: an update launch writes its rows in any order)
+    std::vector<uint8_t> dirty;
     std::vector<Slot> slots;
     std::deque<Pending> waitq;
     std::deque<Step> inflight;
@@ -154,20 +158,30 @@ struct pir_server {
     }
 
     void flush_rows() {
-        if (!pending_rows.n) return;
-        set_rows_kernel<<<1, ROW_UPDATES, 0, st>>>(row_dst_dev, pending_rows);
-        PIR_LAUNCH_CHECK();
-        pending_rows.n = 0;
+        while (!dirty_rows.empty()) {
+            RowUpdates u{};
+            u.n = (uint32_t)std::min<size_t>(ROW_UPDATES, dirty_rows.size());
+            const size_t at = dirty_rows.size() - u.n;
+            for (uint32_t i = 0; i < u.n; ++i) {
+                u.row[i] = dirty_rows[at + i];
+                u.val[i] = row_dst[u.row[i]];
+            }
+            set_rows_kernel<<<1, ROW_UPDATES, 0, st>>>(row_dst_dev, u);
+            PIR_LAUNCH_CHECK();
+            for (uint32_t i = 0; i < u.n; ++i) dirty[u.row[i]] = 0;
+            dirty_rows.resize(at);
+        }
     }
 
+    // (never throws: dirty_rows has room for every row)
     void set_rows(uint32_t s, const uint32_t *out) {
         const uint64_t comp = out ? (uint64_t)db->p.d1 * db->slots() : 0;   // words per component
-        if (pending_rows.n + 2 > ROW_UPDATES) flush_rows();
-        RowUpdates &u = pending_rows;
-        u.row[u.n] = 2 * s;
-        u.val[u.n++] = out ? reinterpret_cast<uint64_t>(out) : 0;
-        u.row[u.n] = 2 * s + 1;
-        u.val[u.n++] = out ? reinterpret_cast<uint64_t>(out + comp) : 0;
+        for (uint32_t c = 0; c < 2; ++c) {
+            const uint32_t row = 2 * s + c;
+            row_dst[row] = out ? reinterpret_cast<uint64_t>(out + c * comp) : 0;
+            if (!dirty[row]) dirty_rows.push_back(row);
+            dirty[row] = 1;
+        }
     }
 
     void retire() {
@@ -220,7 +234,9 @@ struct pir_server {
         flush_rows();
     }
 
-    // launches the next step if any client is active; returns false otherwise
+    // launches the next step if any client is active; returns false otherwise.
+    // The clients' state changes when all of it is on the stream: a step whose
+    // launch fails is launched again.
     bool launch_step() {
         uint32_t hi = 0;
         bool any = false;
@@ -231,15 +247,14 @@ struct pir_server {
             }
         if (!any) return false;
         const uint32_t rows = 2 * (hi + 1);
-        const uint32_t c = (uint32_t)(next_chunk++ % chunks);
+        const uint32_t c = (uint32_t)(next_chunk % chunks);
         const uint32_t g_begin = c * cg, ng = std::min(cg, gall - g_begin);
-        // the tile shape that pads the fewest output words for this many rows
-        // (32 x 256 while at most 16 clients are active: all eight waves on
-        // useful sub-tiles, 256 DB columns per pipeline stage)
-        // (or the query-resident kernel when the rows fill its units)
+        // the kernel of a call with these rows: up to 32 the small-batch one, where
+        // the rows fill its units the query-resident one, else (a short D0, few
+        // columns on a long one, a forced shape) the tiled one in the tile shape
+        // that pads the fewest output words
         const uint32_t mp = (rows + 31) / 32 * 32;
         MfmaJob job;
-        // (or, up to 16 clients, the small-batch kernel)
         if (direct_rows(rows, db->p.d1, db->mfma.kp / 64, ng) && !shape_forced()) {
             job = make_mfma_job(*db, qd, stage, hi + 1, 0, 2);
             job.mp = rows;
@@ -273,27 +288,27 @@ struct pir_server {
         serve_scatter_kernel<<<(uint32_t)blocks, 256, 0, st>>>(stage, row_dst_dev, job.mp, db->p.d1, job.sstride,
                                                                cp, 4 * g_begin, 4 * gall, nblk_n, nblk_p);
         PIR_LAUNCH_CHECK();
-        Step step;
-        for (uint32_t s = 0; s < capacity; ++s) {
-            Slot &sl = slots[s];
-            if (sl.state != ACTIVE) continue;
-            if (--sl.remaining == 0) {
-                sl.state = DRAINING;
-                step.finishing.push_back(s);
-                set_rows(s, nullptr);   // later steps must not write to this request any more
-            }
-        }
-        flush_rows();
         if (spare_events.empty()) {
+            spare_events.reserve(1);
             hipEvent_t e;
             PIR_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
             spare_events.push_back(e);
         }
-        step.ev = spare_events.back();
-        spare_events.pop_back();
-        PIR_HIP(hipEventRecord(step.ev, st));
+        PIR_HIP(hipEventRecord(spare_events.back(), st));
+        Step step{spare_events.back(), {}};
+        for (uint32_t s = 0; s < capacity; ++s)
+            if (slots[s].state == ACTIVE && slots[s].remaining == 1) step.finishing.push_back(s);
         inflight.push_back(std::move(step));
+        spare_events.pop_back();
+        ++next_chunk;
+        for (Slot &sl : slots)
+            if (sl.state == ACTIVE) --sl.remaining;
+        for (const uint32_t s : inflight.back().finishing) {
+            slots[s].state = DRAINING;
+            set_rows(s, nullptr);   // later steps must not write to this request any more
+        }
         ++steps;
+        flush_rows();
         return true;
     }
 };
@@ -349,6 +364,9 @@ pir_status pir_server_create(const pir_db *db, const pir_server_opts *opts, pir_
             PIR_HIP(hipDeviceSynchronize());
             PIR_HIP(hipStreamCreateWithFlags(&srv->st, hipStreamNonBlocking));
             srv->slots.resize(cap);
+            srv->row_dst.resize(srv->mstride);
+            srv->dirty.resize(srv->mstride);
+            srv->dirty_rows.reserve(srv->mstride);
         } catch (...) {
             delete srv;
             throw;
