@@ -392,10 +392,12 @@ static pir_path resolve_path(const pir_db &db, uint32_t B, pir_path path) {
     const bool has_v = db.layouts & PIR_LAYOUT_VALU, has_m = db.layouts & PIR_LAYOUT_MFMA;
     if (path == PIR_PATH_AUTO) {
         // one or two clients are HBM bound: the streaming VALU kernel reads the
-        // DB once at full bandwidth; beyond that the matrix cores win.  With a
-        // prime of 2^30 or more every client is its own streaming pass (two
-        // 64-bit words per sum), so the matrix cores win from two clients on
-        // (8 GiB DB, two 32-bit primes: 1.9 ms on MFMA against 2.8 ms)
+        // DB once at full bandwidth; beyond that the matrix cores win (8 GiB DB,
+        // two 30-bit primes, 1 to 4 clients: 1.29, 1.32, 2.18 and 4.23 ms
+        // streaming, 1.35, 1.42, 1.50 and 1.56 on MFMA).  With a prime of 2^30 or
+        // more every client is its own streaming pass, so the matrix cores win
+        // from two clients on (two 32-bit primes: 1.34 and 2.68 ms streaming, 1.38
+        // and 1.46 on MFMA)
         if (has_v && (!has_m || B <= (db.wide ? 1u : 2u))) return PIR_PATH_VALU;
         return PIR_PATH_MFMA_I8;
     }
@@ -435,6 +437,9 @@ void rowsel_one(const pir_db &db, const uint32_t *q, uint32_t B, uint32_t *out, 
         // 16 clients 9.60 and 2.10 ms; 16 x 300, 12 clients 0.456 and
         // 0.308 ms; 16 x 40, 96 clients 0.379 and 0.437 ms; 24 x 40 0.459 and
         // 0.452 ms; 32 x 40 0.605 and 0.458 ms; 16 x 17, 3 clients 33 and 45 us.
+        // With fewer columns than a unit's 64 the vector ALUs idle as much: 1024 x 1
+        // 3 clients 1.31 and 0.31 ms, 16 clients 1.81 and 0.67 ms (N = 64: 516 and
+        // 44 us, 299 and 52 us); 64 x 16, 3 clients 47 and 39 us (N = 64: 38 and 20).
         const bool cut = path == PIR_PATH_AUTO && B > (db.wide ? 1u : 2u) &&
                          (uint64_t)db.p.d0 * std::min(db.p.d1, 64u) >= 1024;
         auto go = [&](const uint32_t *qn) {

@@ -22,10 +22,11 @@
 //                      coefficient; digits go out as int32 [node][2][ell][N]
 //                      (ell*N words per polynomial instead of L*N residues
 //                      per digit: each limb reduces them on load).  8192
-//                      nodes at N = 4096, four limbs, ell = 5: 0.76-0.88 ms;
-//                      with Gentleman-Sande butterflies, all limbs at once in
-//                      blocks of 1024 threads, and 128-bit sums and
-//                      comparisons per coefficient 0.95-1.1 ms;
+//                      nodes at N = 4096, four limbs, ell = 5: 0.79-0.88 ms
+//                      at 66% of the VALU's issue slots (one wave instruction
+//                      in four cycles); with Gentleman-Sande butterflies, all
+//                      limbs at once in blocks of 1024 threads, and 128-bit
+//                      sums and comparisons per coefficient 1.00-1.22 ms;
 //   multiply-accumulate one block per (node, limb): for each of the 2*ell
 //                      digit polynomials, the residues mod q_l, the forward
 //                      NTT and the product with the two RGSW components of
@@ -33,12 +34,15 @@
 //                      limb's twiddles are staged in LDS, and the next digit
 //                      polynomial is loaded during the current transform);
 //                      then ct0 is added and both output polynomials stored.
-//                      Bound by VALU issue: 8192 nodes at N = 4096, four
-//                      27-bit limbs, ell = 5 take 2.05 ms for 8.1e9
-//                      butterflies, over 80% of the issue slots.  Butterflies
-//                      of six instructions, each twiddle read and waited for
-//                      at its use, four barriers a transform that also waited
-//                      for the loads in flight: 2.42-2.59 ms.
+//                      8192 nodes at N = 4096, four 27-bit limbs, ell = 5:
+//                      2.1-2.4 ms (median 2.34) for 8.1e9 butterflies, 70% of
+//                      the issue slots; the 64-bit multiply-adds, two of a
+//                      butterfly's five instructions, take 4.6 cycles
+//                      instead of four at best, and the waves, two to a SIMD,
+//                      wait for an instruction in 22% of their cycles.
+//                      Butterflies of six instructions, each twiddle read and
+//                      waited for at its use, four barriers a transform that
+//                      also waited for the loads in flight: 2.57-3.07 ms (2.62).
 // The butterfly and sum forms are chosen per launch from the primes: wide
 // (64-bit intermediates) for any prime of 2^30 or more, lazy below, and
 // unreduced forward butterflies when (1 + 2 logN) q < 2^32; the small-ring

@@ -83,7 +83,6 @@ inline uint32_t staging_stride(uint32_t d1) { return (d1 + 3) / 4 * 4; }
 void launch_out_transpose(const uint32_t *stage, uint32_t *out, uint32_t m_rows, uint32_t mp, uint32_t d1,
                           uint32_t slots, hipStream_t st);
 
-void launch_query_digits(const pir_db &db, const uint32_t *q, uint32_t B, int8_t *qd, hipStream_t st);
 void launch_query_digits_rows(const pir_db &db, const uint32_t *q, uint32_t rows, int8_t *qd,
                               uint32_t mstride, uint32_t row0, hipStream_t st);
 // One client each: query q[i] to plane rows row[i] and row[i] + 1.

@@ -14,9 +14,9 @@
 // Barrett reduction at the end yields the canonical residue.
 //
 // Results leave the kernel through a staging buffer [L*N/4][2B][D1] of
-// 16-byte vectors (small outputs directly, see launch_rowsel_stream): every wave stores one contiguous kilobyte with
-// non-temporal stores, and a transpose kernel then writes the boundary
-// layout.  Storing into the boundary layout directly scatters one 16-byte
+// 16-byte vectors (small outputs directly, see launch_rowsel_stream): every
+// wave stores one contiguous kilobyte with non-temporal stores, and a transpose
+// kernel then writes the boundary layout.  Storing into the boundary layout directly scatters one 16-byte
 // piece per lane over as many cache lines, and those partial-line writes,
 // interleaved with the DB stream, cost about a tenth of the kernel's time.
 #include <optional>
@@ -194,10 +194,12 @@ void launch_rowsel_stream(const pir_db &db, const uint32_t *q, uint32_t B, uint3
     const uint32_t nblk_n = (p.d1 + STREAM_THREADS - 1) / STREAM_THREADS;
     const uint64_t blocks = groups * nblk_n;
     // With 32-bit primes the kernel's registers grow with the rows it carries
-    // (two 64-bit words per sum), and beyond one client it runs at low
-    // occupancy: 4 clients in one pass took 15.6 ms on the 8 GiB DB, one pass
-    // per client 1.5 ms each.  So wide DBs take one pass per client, each
-    // re-reading the DB.
+    // (three words per sum): wide DBs take one pass per client, each re-reading
+    // the DB, 1.34 ms of the 8 GiB one.  The line is from the time when a product
+    // took four instructions (4 clients in one pass 15.6 ms); with two, one pass
+    // takes 1.50, 2.70 and 3.49 ms for 2, 3 and 4 clients, so the rule costs the
+    // callers that ask for this path or have no other layout (two clients) up to
+    // 1.2 ms.  The staging of pir_rowsel_noalloc is sized for it.
     const uint32_t rows_per_pass = db.wide ? 2u : 2 * B;
     const uint32_t passes = 2 * B / rows_per_pass;
     const uint64_t C = (uint64_t)rows_per_pass * p.d1;
