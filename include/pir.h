@@ -154,10 +154,10 @@ void pir_db_free(pir_db *db);
  * client is its own pass over the DB) and the INT8 MFMA kernels above; with
  * the VALU layout alone it runs larger batches on the matrix cores too, which
  * cut the records into digits as they read them (unless D0 * min(D1, 64) is
- * below 1024).  On the MFMA path 2B picks the kernel: up to 32 rows (16
- * clients) the small-batch one (from 17 rows on not with fewer than 64 columns
- * and more than 512 DB rows, where there are points enough to fill the tiled
- * one), from 33 rows up, with D0 above 64, the query-resident one (units of 64,
+ * below 1024, or D0 is short, below 16 to 64 rows by B and the primes).  On the
+ * MFMA path 2B picks the kernel: up to 32 rows (16 clients) the small-batch one
+ * (from 17 rows on not with fewer than 64 columns and more than 512 DB rows,
+ * where there are points enough to fill the tiled one), from 33 rows up, with D0 above 64, the query-resident one (units of 64,
  * 96 or 128 rows), else the tiled one;
  * PIR_MFMA_KERNEL=qres or =tile in the environment forces one (tuning and
  * tests; the results are the same bit for bit). */

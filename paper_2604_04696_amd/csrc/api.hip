@@ -407,6 +407,30 @@ static pir_path resolve_path(const pir_db &db, uint32_t B, pir_path path) {
     return path;
 }
 
+// Whether a batch on the VALU layout alone is faster on the matrix cores
+// (rowsel_mfma_valu.hip: units of 64 rows x 64 columns x 16 or 32 query rows, three
+// launches) than on the vector ALUs.  Whole calls, vector ALUs against matrix cores,
+// two limbs: 512 x 512, N = 4096, 3 clients 2.16 and 1.53 ms, 16 clients 9.60 and
+// 2.10 ms.  A handful of records costs less than the padding, whatever the columns
+// (with fewer than a unit's 64 the vector ALUs idle as much: 1024 x 1, N = 4096,
+// 3 clients 1.31 and 0.31 ms, 16 clients 1.81 and 0.67).  One or two clients
+// stream as fast (a client a pass with 32-bit primes), three as fast up to 48 rows
+// (300 columns, us: N = 512 20 rows 19 and 34, 48 rows 33 and 36; N = 2048 70 and
+// 87, 114 and 91), two with 32-bit primes up to 64 (64 columns, N = 4096: 40 rows
+// 38 and 56, 64 rows 54 and 57).  Half a chunk of rows, 32, is enough from there
+// on (N = 512: 17 clients 88 and 78; N = 2048: 4 clients 158 and 96), fewer with
+// 32-bit primes (20 x 300: N = 4096, 5 clients 746 and 210; N = 256, 17 clients 66
+// and 52) and where the query rows fill a unit (N = 512, 12 clients 55 and 51), not
+// with 4 or 17 clients and more (N = 512: 26 and 37; 57 and 77) unless columns and
+// points are many (20 x 128, N = 4096, 40 clients 620 and 362).
+static bool cut_pays(const pir_db &db, uint32_t B) {
+    const auto &p = db.p;
+    if ((uint64_t)p.d0 * std::min(p.d1, 64u) < 1024) return false;
+    if (B <= 3) return B > (db.wide ? 1u : 2u) && p.d0 >= (B == 2 ? 64u : 48u);
+    if (p.d0 >= 32 || db.wide) return true;
+    return B > 4 && (B <= 16 || (p.d1 >= 128 && db.slots() >= 4096));
+}
+
 void check_rowsel_args(const pir_db *db, const uint32_t *q, uint32_t B, const uint32_t *out) {
     PIR_REQUIRE(db != nullptr, "db is NULL");
     if (B == 0) return;
@@ -428,20 +452,9 @@ void rowsel_one(const pir_db &db, const uint32_t *q, uint32_t B, uint32_t *out, 
     if (!q_coeff && env_flag("PIR_VALIDATE")) check_residues(q, qwords, db.p, st);
     const pir_path use = resolve_path(db, B, path);
     if (use == PIR_PATH_VALU) {
-        // A batch on a DB without the MFMA layout, no path asked for: the
-        // matrix cores, which cut the VALU layout's words into digits.  One or
-        // two clients stream as fast without (a client a pass with 32-bit
-        // primes), and a handful of records costs less than the 64 x 64
-        // padding of the units.  Whole calls, vector ALUs against matrix
-        // cores: 512 x 512 (N = 4096, two limbs) 3 clients 2.16 and 1.53 ms,
-        // 16 clients 9.60 and 2.10 ms; 16 x 300, 12 clients 0.456 and
-        // 0.308 ms; 16 x 40, 96 clients 0.379 and 0.437 ms; 24 x 40 0.459 and
-        // 0.452 ms; 32 x 40 0.605 and 0.458 ms; 16 x 17, 3 clients 33 and 45 us.
-        // With fewer columns than a unit's 64 the vector ALUs idle as much: 1024 x 1
-        // 3 clients 1.31 and 0.31 ms, 16 clients 1.81 and 0.67 ms (N = 64: 516 and
-        // 44 us, 299 and 52 us); 64 x 16, 3 clients 47 and 39 us (N = 64: 38 and 20).
-        const bool cut = path == PIR_PATH_AUTO && B > (db.wide ? 1u : 2u) &&
-                         (uint64_t)db.p.d0 * std::min(db.p.d1, 64u) >= 1024;
+        // a batch on a DB without the MFMA layout, no path asked for: the
+        // matrix cores, which cut the VALU layout's words into digits
+        const bool cut = path == PIR_PATH_AUTO && cut_pays(db, B);
         auto go = [&](const uint32_t *qn) {
             if (cut) {
                 try {

@@ -1,8 +1,8 @@
-"""GPU parity of batches on a DB that holds only the VALU layout and has few
-columns on a long D0 (the matrix-core kernel's units of 64 columns, most of them
-past D1), against the CPU oracle, word for word: one column and a few, flushes,
-16- and 32-row units, the first D0 that takes the kernel and the last that does
-not, 30- and 32-bit primes."""
+"""GPU parity of batches on a DB that holds only the VALU layout, against the CPU
+oracle, word for word: few columns on a long D0 (the matrix-core kernel's units of
+64 columns, most of them past D1) with flushes, 16- and 32-row units, 30- and
+32-bit primes; and both sides of each line between that kernel and the vector
+ALUs, over the rows, the clients and the points."""
 import numpy as np
 import pytest
 
@@ -27,6 +27,20 @@ SHAPES = [
     (64, P2, 70, 15, 16),
     (64, synth.PRIMES_W32, 1030, 1, 2),
     (16, synth.PRIMES_W32, 2200, 2, 12),
+    # either side of the lines (matrix cores first)
+    (64, P2, 48, 70, 3),
+    (64, P2, 47, 70, 3),
+    (64, synth.PRIMES_W32, 64, 70, 2),
+    (64, synth.PRIMES_W32, 63, 70, 2),
+    (64, synth.PRIMES_W32, 16, 70, 4),
+    (64, P2, 32, 70, 4),
+    (64, P2, 31, 70, 4),
+    (64, P2, 16, 70, 5),
+    (64, P2, 16, 70, 16),
+    (64, P2, 31, 70, 17),            # (vector ALUs)
+    (2048, P2, 16, 128, 17),
+    (2048, P2, 16, 127, 17),
+    (1024, P2, 16, 128, 17),         # (vector ALUs)
 ]
 
 
