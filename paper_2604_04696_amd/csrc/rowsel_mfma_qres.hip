@@ -48,8 +48,9 @@ constexpr uint32_t QKSUPER = 2048;                  // rows of k per int32 accum
 // RS 16-row sub-tiles per wave, WR row groups of waves, NQ query chunk
 // buffers per block, RING DB chunks per wave (RING - 1 = PF in flight).
 // SHDB: one DB ring for the block (the row groups share the columns),
-// else one per wave.
-template <int RS_, int WR_, int NQ_, int RING_, bool SHDB_ = false, int RN_ = 1>
+// else one per wave.  LATE: with the shared ring, a step's loads are issued
+// after the first query digit's MFMAs, else before them.
+template <int RS_, int WR_, int NQ_, int RING_, bool SHDB_ = false, int RN_ = 1, bool LATE_ = SHDB_>
 struct QShape {
     static constexpr int RS = RS_;
     static constexpr int RN = RN_;                       // 16-column sub-tiles per wave
@@ -57,6 +58,7 @@ struct QShape {
     static constexpr int NQ = NQ_;
     static constexpr int RING = RING_;
     static constexpr bool SHDB = SHDB_;
+    static constexpr bool LATE = LATE_;
     static constexpr int PF = RING - 1;
     static constexpr int BM = 16 * RS * WR;              // query rows of a unit
     static constexpr int WC = QWAVES / WR;               // waves per row group
@@ -71,6 +73,7 @@ struct QShape {
     static_assert(DB_LDS + RING * DBS <= LDS_BYTES, "LDS");
     static_assert(PF >= 1 && (SHDB || (PF <= NQ && PF >= NQ - 1)) && NQ >= 2, "pipeline depths");
     static_assert(RN == 1 || SHDB, "a wave's own DB ring holds 16 columns");
+    static_assert(SHDB || !LATE, "the waits of a wave's own ring count its loads as issued first");
 };
 
 template <int N>
@@ -122,9 +125,8 @@ __device__ __forceinline__ QUnit decode_unit(uint32_t u, const MfmaJob &J, uint3
 //      the block at a barrier, after which the buffers read in step t - 1
 //      are free;
 //   2. issues its loads of query chunk t + NQ - 1 and of DB chunk t + PF
-//      (PF = RING - 1) into those buffers (with the shared DB ring after the
-//      first query digit's MFMAs, so that their addresses are worked out
-//      under them: 64 clients on 8 GiB 4.16 -> 4.07 ms);
+//      (PF = RING - 1) into those buffers (LATE: after the first query
+//      digit's MFMAs, so that their addresses are worked out under them);
 //   3. with its own DB ring, waits for its DB chunk t (PF steps' loads were
 //      issued after it; in the first PF steps it waits for everything);
 //   4. reads the four digits' B fragments and, per query digit, the RS A
@@ -308,6 +310,11 @@ rowsel_mfma_qres_kernel(const MfmaJob J) {
             else qwait_vmcnt<AFTER_BOTH>();
             ++gstep;
             qbarrier();
+            // 2.
+            if (!S::LATE) {
+                q_issue();
+                d_issue();
+            }
         } else {
             // 1. query chunk t: after its loads, this wave issued one step's
             //    DB loads and NQ - 2 steps' query and DB loads
@@ -355,7 +362,7 @@ rowsel_mfma_qres_kernel(const MfmaJob J) {
                         acc[i + j][rs * RN + rn] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
                             a[i % 2][rs], b[j][rn], acc[i + j][rs * RN + rn], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
-            if (SHDB && i == 0) {
+            if (S::LATE && i == 0) {   // 2.
                 q_issue();
                 d_issue();
                 __builtin_amdgcn_sched_barrier(0);
@@ -494,7 +501,18 @@ void launch_mfma_qres(const MfmaJob &job, hipStream_t st) {
         case 0: go_mode(QShape<2, 1, 3, 4>{}); break;
         case 1: go_mode(QShape<2, 2, 3, 3, true, 2>{}); break;
         case 2: go_mode(QShape<3, 2, 3, 3, true>{}); break;
-        default: go_mode(QShape<2, 4, 2, 3, true, 2>{}); break;
+        default:
+            // The 128-row unit holds two query chunks, so its next one is due a
+            // step after it is asked for: issued before the first products unless
+            // k is long and the units of a point share it through the L2, where
+            // the products are the bound.  GEMM alone, issued first against after
+            // them: 512 x 512, N = 4096, 64 clients 4.04 and 3.94 ms; 1024 x 64
+            // 1.31 and 1.35; 65 x 512 1.35 and 1.39; 300 x 32, 100 clients 0.67
+            // and 0.70.  (The units of 64 and 96 rows hold three: 1-3% faster
+            // after, whatever the shape.)
+            if (job.nblk_n > 2 && job.nkc >= 8) go_mode(QShape<2, 4, 2, 3, true, 2, true>{});
+            else go_mode(QShape<2, 4, 2, 3, true, 2, false>{});
+            break;
     }
     PIR_LAUNCH_CHECK();
 }
