@@ -149,7 +149,15 @@ rowsel_mfma_qres_kernel(const MfmaJob J) {
 
     const uint32_t lane = threadIdx.x % 64;
     const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
-    const uint32_t wr = wv / S::WC, wc = wv % S::WC;
+    const uint32_t wr = wv / S::WC;
+    // With two row groups of four waves and at most half a unit's columns, the
+    // waves whose outputs are stored have wc 0 and 1 in both: the second group's
+    // order is turned by two so that they sit on all four SIMDs (wave w is on SIMD
+    // w % 4) and a flush takes half as long (65 x 64, N = 4096, 32 clients, 169 ->
+    // 155 us; 32-bit primes 187 -> 163).  Not with several units a point: one
+    // that is done sooner runs ahead of the others, and the query planes no
+    // longer come from the L2 (1024 x 192, 32 clients, 7% slower).
+    const uint32_t wc = (wv % S::WC) ^ (WR == 2 && J.nblk_n == 1 ? 2 * wr : 0);
     const uint32_t per_xcd = gridDim.x / 8, xcd = blockIdx.x % 8, yi = blockIdx.x / 8;
     auto unit_of = [&](uint32_t i) { return (i * 8 + xcd) * per_xcd + yi; };
     const uint32_t units = J.tiles, nkc = J.nkc, d1 = J.d1;
